@@ -64,4 +64,114 @@ inline FarChunks far_chunks(int N, int nsplit) {
   return {s1, (int)c1, (int)c2};
 }
 
+// ---- sums with every unordered pair of points evaluated once (k_far_sym.hip) -----------
+// nb blocks of tb points; block row i pairs with the h next blocks (cyclic), rows of the nb in
+// phases of `rows`.  In a phase that starts at row0 the blocks row0 .. row0 + nj - 1 (cyclic) are
+// cut into chunks, the first nl of them of csl points and the rest, which run last and let
+// the grid drain, of css.  `slots` bounds the chunks of one row.
+struct SymPlan {
+  int tb, nb, h, csl, css, lead, rows;  // lead: per cent of a phase's blocks that take csl
+};
+struct SymPhase {
+  int rows, nj, nl, chunks, slots, width;  // width: most rows of the phase that pair with one block
+};
+
+// Row (from row0) of the phase at place x among those that pair with block jr (from row0), or -1.
+// The grid holds these pairs alone: with a place for every row of the phase half of them
+// would leave at once, and where the number of rows is a multiple of 32 the rest fall on half
+// of the shader engines, which take workgroups in turn (24,000 points, 32 rows: 0.61 ms
+// instead of 0.41).
+#ifdef __HIPCC__
+__host__ __device__
+#endif
+inline int sym_row(int jr, int x, int nb, int h, int rows) {
+  if (h + rows >= nb) {  // the phase's blocks are all nb, cyclic
+    const int r = jr - x;
+    return r >= 0 ? (r < rows ? r : -1) : (r + nb < rows ? r + nb : -1);
+  }
+  const int r = (jr < rows ? jr : rows - 1) - x;
+  return r >= 0 && jr - r <= h ? r : -1;
+}
+
+inline SymPhase sym_phase(const SymPlan& sp, int rows) {
+  SymPhase p;
+  p.rows = rows;
+  p.nj = std::min(sp.nb, sp.h + rows);
+  p.nl = (int)((long)p.nj * sp.lead / 100);
+  const int pl = sp.tb / sp.csl, ps = sp.tb / sp.css;
+  p.chunks = p.nl * pl + (p.nj - p.nl) * ps;
+  p.width = p.nj == sp.nb ? sp.h + 1 : std::min(rows, sp.h + 1);
+  p.slots = (1 + sp.h) * pl + (ps - pl) * std::min(1 + sp.h, p.nj - p.nl);
+  return p;
+}
+
+// Doubles of scratch one phase needs, nv values per point: the chunks' sums of the row's
+// points and the sums of the points at the other end.
+inline size_t sym_need(const SymPlan& sp, int rows, int nv) {
+  return (size_t)rows * nv * sp.tb * (sym_phase(sp, rows).slots + sp.h);
+}
+
+// Scratch (doubles) these sums may use at N points, non-decreasing in N: 120 MiB below 28,672
+// points, which the scratch of the no-allocation entry point holds too, so that both run the
+// same phases there; above, about what a single phase takes, up to 2 GiB.
+constexpr int kSymMin = 15000;
+inline size_t sym_cap(size_t N) {
+  if (N < (size_t)kSymMin) return 0;
+  constexpr double kMiB = 131072.0;  // doubles
+  if (N < 28672) return (size_t)(120.0 * kMiB);
+  const double f = (double)N / 73728.0;
+  return (size_t)std::min(std::max(256.0 * kMiB, 300.0 * kMiB * f * f), 2048.0 * kMiB);
+}
+
+// Plan for N points within `cap` doubles of scratch; rows = 0 where the ordered sum is to be
+// used.  kind: 0 traction, 1 Stokeslet, 2 and 3 Laplace, 4 traction + Stokeslet; prec: 0
+// float64, 1 float32.  Where the line lies, measured on MI355X (ms, the ordered sum with its
+// combine against this one with its reduction): float64 traction 0.149 / 0.150 at 12,000
+// points, 0.250 / 0.216 at 16,000, 0.475 / 0.408 at 24,000, 4.30 / 3.30 at 73,728 and 20.1 / 15.7
+// at 160,000; Stokeslet 0.134 / 0.139, 0.225 / 0.203, 0.432 / 0.380, 3.87 / 3.12; Laplace normal
+// derivative 3.07 / 2.09 and single layer 2.34 / 1.39 at 73,728; the fused sum 0.483 / 0.496 at
+// 20,000, 4.04 / 3.75 at 60,000 and 29.0 / 25.5 at 160,000 (its six sums a side leave two waves
+// per SIMD); float32 traction 0.177 / 0.178 at 20,000, 0.606 / 0.572 at 40,000 and 9.34 / 8.41 at
+// 160,000 (its ordered kernel issues nearly two VALU operations per four cycles with eight
+// waves per SIMD, more than the six waves here reach, which eats half of the gain).
+inline SymPlan sym_plan(int N, int kind, int prec, size_t cap) {
+  SymPlan sp{};
+  const int from = prec ? 36000 : kind == 4 ? 56000 : kSymMin;
+  if (N < from || (prec && kind > 1)) return sp;
+  sp.tb = kind == 0 && !prec && N >= 50000 ? 1536 : kind == 2 || kind == 3 ? 1024 : 768;
+  sp.nb = (int)(((long)N + sp.tb - 1) / sp.tb);
+  sp.h = sp.nb / 2;
+  const int nv = kind == 4 ? 6 : kind >= 2 ? 1 : 3;
+  // chunks (long, short, per cent long) by size: many short ones keep the chip busy at the
+  // small end, few long ones spare partial sums at the large one; where the size's own
+  // choice does not fit the scratch in one phase the next coarser is taken, then phases
+  constexpr int kClasses = 5;
+  const int upto[kClasses] = {32000, 50000, 100000, 300000, 2147483647};
+  const int c768[kClasses][3] = {{192, 64, 75}, {384, 128, 85}, {768, 128, 80}, {768, 192, 85}, {768, 192, 90}};
+  const int c1024[kClasses][3] = {{128, 64, 75}, {256, 128, 80}, {512, 128, 80}, {512, 256, 90}, {1024, 256, 90}};
+  int cls = 0, lo = 0;
+  while (N >= upto[cls]) ++cls;
+  for (;; ++cls) {
+    const int* c = sp.tb == 1024 ? c1024[cls] : c768[cls];
+    sp.csl = cls == 4 && sp.tb == 1536 ? 1536 : c[0];
+    sp.css = c[1];
+    sp.lead = c[2];
+    lo = 0;
+    int hi = sp.nb;  // most rows that fit
+    while (lo < hi) {
+      const int mid = lo + (hi - lo + 1) / 2;
+      if (sym_need(sp, mid, nv) <= cap) lo = mid; else hi = mid - 1;
+    }
+    if (lo == sp.nb || cls == kClasses - 1 || (cls == 3 && lo > 0)) break;
+  }
+  if (lo < 1) return SymPlan{};
+  const int phases = (sp.nb + lo - 1) / lo;
+  sp.rows = (sp.nb + phases - 1) / phases;
+  // every phase drains the chip once: two rounds of 512 long chunks in each, or the ordered
+  // sum; and the grid's second dimension holds 65,535 chunks
+  if ((phases > 1 && (long)sp.rows * (1 + sp.h) * (sp.tb / sp.csl) < 2 * 512) || sym_phase(sp, sp.rows).chunks > 65535)
+    return SymPlan{};
+  return sp;
+}
+
 }  // namespace rbm

@@ -172,11 +172,12 @@ template hipError_t launch_far<double>(int, int, int, const double*, const doubl
 template hipError_t launch_far<float>(int, int, int, const float*, const float*, const void*,
                                       double*, int, hipStream_t);
 
-// q_g = W_g * z_g (z rotated to the lab frame first when given in body frames).
+// q_g = W_g * z_g (z rotated to the lab frame first when given in body frames); with nor the
+// normals Nn are packed too.
 template <typename T>
 __global__ void k_pack(int N, int M, const double* __restrict__ X, const double* __restrict__ W,
                        const double* __restrict__ Rm, const double* __restrict__ z, int z_is_body,
-                       double* __restrict__ zlab, Src8<T>* __restrict__ src) {
+                       const double* __restrict__ Nn, Src8<T>* __restrict__ src, Nor4<T>* __restrict__ nor) {
   const int g = blockIdx.x * blockDim.x + threadIdx.x;
   if (g >= N) return;
   double v0 = z[g], v1 = z[N + g], v2 = z[2 * (size_t)N + g];
@@ -186,11 +187,6 @@ __global__ void k_pack(int N, int M, const double* __restrict__ X, const double*
     const double a1 = R[3] * v0 + R[4] * v1 + R[5] * v2;
     const double a2 = R[6] * v0 + R[7] * v1 + R[8] * v2;
     v0 = a0; v1 = a1; v2 = a2;
-  }
-  if (zlab) {
-    zlab[g] = v0;
-    zlab[N + g] = v1;
-    zlab[2 * (size_t)N + g] = v2;
   }
   const double w = W ? W[g] : 1.0;
   Src8<T> s;
@@ -203,23 +199,31 @@ __global__ void k_pack(int N, int M, const double* __restrict__ X, const double*
   s.v[6] = 0;
   s.v[7] = 0;
   src[g] = s;
+  if (nor) {
+    Nor4<T> m;
+    m.v[0] = (T)Nn[g];
+    m.v[1] = (T)Nn[N + g];
+    m.v[2] = (T)Nn[2 * (size_t)N + g];
+    m.v[3] = 0;
+    nor[g] = m;
+  }
 }
 
 template <typename T>
 hipError_t launch_pack_sources(int N, int M, const double* X, const double* W, const double* Rm,
-                               const double* z, int z_is_body, double* z_lab_out, void* src,
+                               const double* z, int z_is_body, const double* Nn, void* src, void* nor,
                                hipStream_t st) {
-  k_pack<T><<<(N + 255) / 256, 256, 0, st>>>(N, M, X, W, Rm, z, z_is_body, z_lab_out,
-                                             reinterpret_cast<Src8<T>*>(src));
+  k_pack<T><<<(N + 255) / 256, 256, 0, st>>>(N, M, X, W, Rm, z, z_is_body, Nn,
+                                             reinterpret_cast<Src8<T>*>(src), reinterpret_cast<Nor4<T>*>(nor));
   return hipGetLastError();
 }
 
 template hipError_t launch_pack_sources<double>(int, int, const double*, const double*,
-                                                const double*, const double*, int, double*, void*,
-                                                hipStream_t);
+                                                const double*, const double*, int, const double*, void*,
+                                                void*, hipStream_t);
 template hipError_t launch_pack_sources<float>(int, int, const double*, const double*,
-                                               const double*, const double*, int, double*, void*,
-                                               hipStream_t);
+                                                const double*, const double*, int, const double*, void*,
+                                                void*, hipStream_t);
 
 // out = ca*a + cb*(R_i b_body) + cp*sum_s part[s]   (fixed summation order); out may be
 // a, not b_body.  The slot sum over the split is the memory-bound part.

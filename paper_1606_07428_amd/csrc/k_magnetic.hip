@@ -204,9 +204,10 @@ __global__ __launch_bounds__(256) void k_scalar_self(int n, int M, const int* __
   y[e] = v;
 }
 
-// Packed scalar sources: (x, y, z, w q, 0, 0, 0, 0).
+// Packed scalar sources: (x, y, z, w q, 0, 0, 0, 0), and normals (nx, ny, nz, 0).
 __global__ void k_pack_scalar(int N, const double* __restrict__ X, const double* __restrict__ W,
-                              const double* __restrict__ q, Src8<double>* __restrict__ src) {
+                              const double* __restrict__ q, const double* __restrict__ Nn,
+                              Src8<double>* __restrict__ src, Nor4<double>* __restrict__ nor) {
   const int g = blockIdx.x * blockDim.x + threadIdx.x;
   if (g >= N) return;
   Src8<double> s;
@@ -216,6 +217,12 @@ __global__ void k_pack_scalar(int N, const double* __restrict__ X, const double*
   s.v[3] = W[g] * q[g];
   s.v[4] = s.v[5] = s.v[6] = s.v[7] = 0.0;
   src[g] = s;
+  Nor4<double> m;
+  m.v[0] = Nn[g];
+  m.v[1] = Nn[N + g];
+  m.v[2] = Nn[2 * (size_t)N + g];
+  m.v[3] = 0.0;
+  nor[g] = m;
 }
 
 // out = cv v + cs self + cp sum_s part[s][0][g] (first component of the split slots).
@@ -316,9 +323,10 @@ hipError_t launch_scalar_self(int n, int M, const int* sid, const double* A, con
   return hipGetLastError();
 }
 
-hipError_t launch_pack_scalar(int N, const double* X, const double* W, const double* q, void* src,
-                              hipStream_t st) {
-  k_pack_scalar<<<(N + 255) / 256, 256, 0, st>>>(N, X, W, q, reinterpret_cast<Src8<double>*>(src));
+hipError_t launch_pack_scalar(int N, const double* X, const double* W, const double* q, const double* Nn,
+                              void* src, void* nor, hipStream_t st) {
+  k_pack_scalar<<<(N + 255) / 256, 256, 0, st>>>(N, X, W, q, Nn, reinterpret_cast<Src8<double>*>(src),
+                                                 reinterpret_cast<Nor4<double>*>(nor));
   return hipGetLastError();
 }
 

@@ -85,10 +85,10 @@ hipError_t launch_self_apply_shared(int n, int M, const TM* A, const double* Rm,
 
 // ---- far field (k_far.hip) -------------------------------------------------------
 // Pack sources: (X_g, q_g) with q_g = W_g * (R_i z_body or z_lab)[g] into AoS of T.
-// If z_lab_out != nullptr the rotated z is also written (lab frame, float64).
+// If nor != nullptr the normals Nn are packed into it (nx, ny, nz, 0).
 template <typename T>
 hipError_t launch_pack_sources(int N, int M, const double* X, const double* W, const double* Rm,
-                               const double* z, int z_is_body, double* z_lab_out, void* src,
+                               const double* z, int z_is_body, const double* Nn, void* src, void* nor,
                                hipStream_t st);
 // kind 0 = traction (targets need normals), 1 = Stokeslet.  Writes nsplit partial sums
 // part[nsplit][3][N] (float64).  Returns the split used through *nsplit_out.
@@ -99,6 +99,14 @@ hipError_t launch_far(int kind, int N, int M, const T* tx, const T* nrm, const v
 // same packed sources in one pass, nsplit partial sums each
 hipError_t launch_far_ts(int N, int M, const double* tx, const double* nrm, const void* src, double* part_t,
                          double* part_u, int nsplit, hipStream_t st);
+// The sums of the packed points src, nor (nor unused by kinds 1 and 3) with every unordered pair
+// evaluated once, by the plan sp of far_plan.h: totals (not partial sums) into out0 and, for
+// kind 4 (traction and Stokeslet), the Stokeslet part into out1.  part: the plan's scratch,
+// which must not overlap the outputs.  Kinds 0, 1, 4 as above, 2 and 3 the scalar Laplace sums.
+struct SymPlan;
+template <typename T>
+hipError_t launch_far_sym(int kind, const SymPlan& sp, int N, int M, const void* src, const void* nor, double* part,
+                          double* out0, double* out1, hipStream_t st);
 // out[3][N] = ca * a[3][N] (optional) + cb * R_i b_body (optional) + cp * sum_s part[s];
 // out may be the same array as a, never as b_body
 hipError_t launch_combine(int N, int M, int nsplit, const double* part, double cp,
@@ -227,7 +235,8 @@ hipError_t launch_magnetic_tables(int p, int ns, const double* coef, const doubl
 // y = A_{s(i)} x per body, scalar node vectors
 hipError_t launch_scalar_self(int n, int M, const int* sid, const double* A, const double* x, double* y,
                               hipStream_t st);
-hipError_t launch_pack_scalar(int N, const double* X, const double* W, const double* q, void* src,
+hipError_t launch_pack_scalar(int N, const double* X, const double* W, const double* q, const double* Nn,
+                              void* src, void* nor,
                               hipStream_t st);
 // out = cv v + cs self + cp sum of the split slots' first component (v, self may be NULL)
 hipError_t launch_scalar_combine(int N, int nsplit, const double* part, double cp, const double* self,

@@ -8,6 +8,8 @@
 namespace rbm {
 
 template <typename T> struct alignas(8 * sizeof(T)) Src8 { T v[8]; };
+// Packed normal of the same point (nx, ny, nz, 0), for the sums that need it at the source.
+template <typename T> struct alignas(4 * sizeof(T)) Nor4 { T v[4]; };
 
 // 1/sqrt(x) in float64: hardware estimate plus one third-order correction
 // y <- y + y e (1/2 + 3/8 e), e = 1 - x y^2 (error cubes each step).  Used by the

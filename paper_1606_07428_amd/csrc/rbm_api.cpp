@@ -90,6 +90,7 @@ struct rbm_ctx {
   // far field; part_u holds the Stokeslet partial sums of a fused residual evaluation,
   // valid for the current mu while vel_ready
   void* src;
+  void* nor;
   double* part;
   double* part_u = nullptr;
   bool vel_ready = false;
@@ -122,7 +123,9 @@ struct rbm_ctx {
   double fmm_lo[3] = {0, 0, 0}, fmm_D = 1.0;
   size_t fmm_off[8] = {0};
   int* fmm_cnt[8] = {nullptr};
-  int far_nslots = 0, far_base = 0;  // partial-sum slots of the last far sum, near slot index
+  // partial-sum slots of the last far sum (near slot included), near slot index, and the slots
+  // of the Stokeslet half of a fused pass
+  int far_nslots = 0, far_base = 0, vel_nslots = 0;
   // contact search: coarse bounding radius per shape (device and host), candidate pairs
   double *rbc = nullptr, *cres = nullptr;
   int* ccand = nullptr;
@@ -297,6 +300,21 @@ static int split_for(const rbm_ctx* c, int N) {
   return s;
 }
 
+// Sum of kind (0 traction, 1 Stokeslet, 2 and 3 Laplace) over the N points packed in c->src and
+// c->nor, precision prec, into partial-sum slots at c->part; returns their number.  The target
+// arrays (float64 or float32 by prec) serve the ordered sum.  Every unordered pair once where
+// sym_plan says so (its total is one slot; the scratch lies behind two of them).
+template <typename T>
+static hipError_t far_sum(rbm_ctx* c, int kind, int N, int M, const T* tx, const T* tn, int* nslots) {
+  const SymPlan sp = sym_plan(N, kind, sizeof(T) == 8 ? 0 : 1, sym_cap(N));
+  if (sp.rows > 0) {
+    *nslots = 1;
+    return launch_far_sym<T>(kind, sp, N, M, c->src, c->nor, c->part + 6 * (size_t)N, c->part, nullptr, c->st);
+  }
+  *nslots = split_for(c, N);
+  return launch_far<T>(kind, N, M, tx, tn, c->src, c->part, *nslots, c->st);
+}
+
 // Bump allocation over the bound workspace; with assign == false only sizes.
 static size_t layout(rbm_ctx* c, int nmax, bool assign) {
   size_t off = 0;
@@ -346,7 +364,11 @@ static size_t layout(rbm_ctx* c, int nmax, bool assign) {
   double* srcd = nullptr;
   take(srcd, 8 * N);
   if (assign) c->src = srcd;
-  take(c->part, 3 * (far_part_cap(N) + (c->pu ? N : 0)));
+  take(srcd, 4 * N);
+  if (assign) c->nor = srcd;
+  // partial sums of the ordered sums, or two slots and the scratch of the sums that take every
+  // pair once
+  take(c->part, std::max(3 * (far_part_cap(N) + (c->pu ? N : 0)), 6 * N + sym_cap(N)));
   take(c->part_u, 3 * (far_part_cap(N) + (c->pu ? N : 0)));
   take(c->ccand, 2 * (size_t)kContactCand * nm); take(c->cres, 5 * (size_t)kContactCand * nm);
   if (c->opt.magnetic) {
@@ -651,10 +673,6 @@ struct SolveState {
   int fmm_applies = 0;
 };
 
-// Partial-sum slots the combine adds for N points: the far sum's split plus, with
-// upsampling, the near-correction slot that follows it.
-static int far_slots(const rbm_ctx* c, int N) { return split_for(c, N) + (c->pu ? 1 : 0); }
-
 // Near-singular correction of the far sum of kind (0 traction, 1 Stokeslet) for the
 // density x whose plain sources are already packed in c->src: fine sources of the needed
 // bodies, fine-minus-plain sums per work item, reduced per body into the slot after the
@@ -766,9 +784,8 @@ static rbm_status fmm_apply(rbm_ctx* c, int prec, double* out) {
 static rbm_status far_traction(rbm_ctx* c, SolveState& S, const double* x, int x_is_body,
                                int prec) {
   const int N = c->n * c->M;
-  const int nsp = split_for(c, N);
   if (prec != 0 && c->fmm_ready && c->fmm_npts == N) {
-    HIPCHECK(launch_pack_sources<float>(N, c->M, c->X, c->W, c->Rm, x, x_is_body, nullptr, c->src, c->st));
+    HIPCHECK(launch_pack_sources<float>(N, c->M, c->X, c->W, c->Rm, x, x_is_body, nullptr, c->src, nullptr, c->st));
     Timer t(c);
     rbm_status s = fmm_apply(c, 1, c->part);
     if (s != RBM_OK) return s;
@@ -779,21 +796,20 @@ static rbm_status far_traction(rbm_ctx* c, SolveState& S, const double* x, int x
     S.fmm_applies++;
     return near_correction(c, S, 0, x, x_is_body, 1);
   }
-  c->far_base = nsp;
-  c->far_nslots = nsp + (c->pu ? 1 : 0);
   if (prec == 0) {
-    HIPCHECK(launch_pack_sources<double>(N, c->M, c->X, c->W, c->Rm, x, x_is_body, nullptr, c->src, c->st));
+    HIPCHECK(launch_pack_sources<double>(N, c->M, c->X, c->W, c->Rm, x, x_is_body, c->Nn, c->src, c->nor, c->st));
     Timer t(c);
-    HIPCHECK(launch_far<double>(0, N, c->M, c->X, c->Nn, c->src, c->part, nsp, c->st));
+    HIPCHECK(far_sum<double>(c, 0, N, c->M, c->X, c->Nn, &c->far_base));
     t.stop();
     if (t.on) S.trac_ev.push_back({c->ev_used - 2, c->ev_used - 1});
   } else {
-    HIPCHECK(launch_pack_sources<float>(N, c->M, c->X, c->W, c->Rm, x, x_is_body, nullptr, c->src, c->st));
+    HIPCHECK(launch_pack_sources<float>(N, c->M, c->X, c->W, c->Rm, x, x_is_body, c->Nn, c->src, c->nor, c->st));
     Timer t(c);
-    HIPCHECK(launch_far<float>(0, N, c->M, c->Xf, c->Nf, c->src, c->part, nsp, c->st));
+    HIPCHECK(far_sum<float>(c, 0, N, c->M, c->Xf, c->Nf, &c->far_base));
     t.stop();
     if (t.on) S.trac32_ev.push_back({c->ev_used - 2, c->ev_used - 1});
   }
+  c->far_nslots = c->far_base + (c->pu ? 1 : 0);
   S.far_pairs += (double)N * N - (double)c->n * c->M * c->M;
   return near_correction(c, S, 0, x, x_is_body, prec == 0 ? 0 : 1);
 }
@@ -1008,15 +1024,20 @@ static rbm_status residual_exact(rbm_ctx* c, SolveState& S, const double* x, dou
   if ((s = self_apply(c, S, 0, 0, tmp, c->yb)) != RBM_OK) return s;
   c->vel_ready = false;
   if (velocity) {
-    const int nsp = split_for(c, N);
-    HIPCHECK(launch_pack_sources<double>(N, M, c->X, c->W, c->Rm, tmp, 0, nullptr, c->src, st));
+    HIPCHECK(launch_pack_sources<double>(N, M, c->X, c->W, c->Rm, tmp, 0, c->Nn, c->src, c->nor, st));
+    const SymPlan sp = sym_plan(N, 4, 0, sym_cap(N));
     Timer t(c);
-    HIPCHECK(launch_far_ts(N, M, c->X, c->Nn, c->src, c->part, c->part_u, nsp, st));
+    if (sp.rows > 0) {
+      c->far_base = 1;
+      HIPCHECK(launch_far_sym<double>(4, sp, N, M, c->src, c->nor, c->part + 6 * (size_t)N, c->part, c->part_u, st));
+    } else {
+      c->far_base = split_for(c, N);
+      HIPCHECK(launch_far_ts(N, M, c->X, c->Nn, c->src, c->part, c->part_u, c->far_base, st));
+    }
     t.stop();
     if (t.on) S.fused_ev.push_back({c->ev_used - 2, c->ev_used - 1});
     S.far_pairs += 2.0 * ((double)N * N - (double)n * M * M);
-    c->far_base = nsp;
-    c->far_nslots = nsp + (c->pu ? 1 : 0);
+    c->far_nslots = c->vel_nslots = c->far_base + (c->pu ? 1 : 0);
     if ((s = near_correction(c, S, 0, tmp, 0, 0)) != RBM_OK) return s;
     if ((s = near_correction(c, S, 1, tmp, 0, 0, c->part_u)) != RBM_OK) return s;
     c->vel_ready = true;
@@ -1201,18 +1222,18 @@ static rbm_status solve_impl(rbm_ctx* c, const double* dFT, double* dVW, rbm_sol
   HIPCHECK(launch_axpby(len, 1.0, c->rho, 1.0, c->mu, c->t2, st));
   if (c->vel_ready) {
     S.fused_used = true;
-    HIPCHECK(launch_combine(N, M, far_slots(c, N), c->part_u, 1.0 / c->opt.eta, nullptr, 0.0, nullptr, nullptr,
+    HIPCHECK(launch_combine(N, M, c->vel_nslots, c->part_u, 1.0 / c->opt.eta, nullptr, 0.0, nullptr, nullptr,
                             0.0, c->t1, st));
   } else {
-    HIPCHECK(launch_pack_sources<double>(N, M, c->X, c->W, c->Rm, c->t2, 0, nullptr, c->src, st));
+    HIPCHECK(launch_pack_sources<double>(N, M, c->X, c->W, c->Rm, c->t2, 0, nullptr, c->src, nullptr, st));
     Timer t(c);
-    HIPCHECK(launch_far<double>(1, N, M, c->X, nullptr, c->src, c->part, split_for(c, N), st));
+    HIPCHECK(far_sum<double>(c, 1, N, M, c->X, nullptr, &c->far_base));
     t.stop();
     if (t.on) S.stok_ev.push_back({c->ev_used - 2, c->ev_used - 1});
     S.far_pairs += (double)N * N - (double)n * M * M;
-    c->far_base = split_for(c, N);
+    c->far_nslots = c->far_base + (c->pu ? 1 : 0);
     if ((s = near_correction(c, S, 1, c->t2, 0, 0)) != RBM_OK) return s;
-    HIPCHECK(launch_combine(N, M, far_slots(c, N), c->part, 1.0 / c->opt.eta, nullptr, 0.0, nullptr, nullptr,
+    HIPCHECK(launch_combine(N, M, c->far_nslots, c->part, 1.0 / c->opt.eta, nullptr, 0.0, nullptr, nullptr,
                             0.0, c->t1, st));
   }
   c->vel_ready = false;
@@ -1522,10 +1543,10 @@ extern "C" rbm_status rbm_solve_density_dev(rbm_ctx* c, const double* d_rho, dou
 // w = 1/2 v + eta (K^L_self v + K^L_far v) on scalar node vectors (float64).
 static rbm_status magnetic_apply(rbm_ctx* c, double eta, const double* v, double* w) {
   const int n = c->n, M = c->M, N = n * M;
-  const int nsp = split_for(c, N);
+  int nsp = 0;
   HIPCHECK(launch_scalar_self(n, M, c->sid, c->KL0, v, c->mtmp, c->st));
-  HIPCHECK(launch_pack_scalar(N, c->X, c->W, v, c->src, c->st));
-  HIPCHECK(launch_far<double>(2, N, M, c->X, c->Nn, c->src, c->part, nsp, c->st));
+  HIPCHECK(launch_pack_scalar(N, c->X, c->W, v, c->Nn, c->src, c->nor, c->st));
+  HIPCHECK(far_sum<double>(c, 2, N, M, c->X, c->Nn, &nsp));
   HIPCHECK(launch_scalar_combine(N, nsp, c->part, eta, c->mtmp, eta, v, 0.5, w, c->st));
   return RBM_OK;
 }
@@ -1599,7 +1620,7 @@ static rbm_status magnetic_traction_impl(rbm_ctx* c, const double* H0, double mu
                                          double tol, double* d_rho, double* d_FT, int* iters) {
   rbm_status s;
   const int n = c->n, M = c->M, N = n * M;
-  const int nsp = split_for(c, N);
+  int nsp = 0;
   const double eta = (mu_ratio - 1.0) / (mu_ratio + 1.0);
   hipStream_t st = c->st;
   // q from (1/2 I + eta K^L) q = eta H0 . n
@@ -1609,13 +1630,13 @@ static rbm_status magnetic_traction_impl(rbm_ctx* c, const double* H0, double mu
   if (iters) *iters = it;
   // phi = -H0 . X + S^L q
   HIPCHECK(launch_scalar_self(n, M, c->sid, c->SL0, c->mq, c->mtmp, st));
-  HIPCHECK(launch_pack_scalar(N, c->X, c->W, c->mq, c->src, st));
-  HIPCHECK(launch_far<double>(3, N, M, c->X, c->Nn, c->src, c->part, nsp, st));
+  HIPCHECK(launch_pack_scalar(N, c->X, c->W, c->mq, c->Nn, c->src, c->nor, st));
+  HIPCHECK(far_sum<double>(c, 3, N, M, c->X, c->Nn, &nsp));
   HIPCHECK(launch_scalar_combine(N, nsp, c->part, 1.0, c->mtmp, 1.0, nullptr, 0.0, c->mphi, st));
   HIPCHECK(launch_hdot(N, c->X, H0[0], H0[1], H0[2], -1.0, 1, c->mphi, st));
   // exterior normal derivative dn = -H0 . n - q/2 + K^L q
   HIPCHECK(launch_scalar_self(n, M, c->sid, c->KL0, c->mq, c->mtmp, st));
-  HIPCHECK(launch_far<double>(2, N, M, c->X, c->Nn, c->src, c->part, nsp, st));
+  HIPCHECK(far_sum<double>(c, 2, N, M, c->X, c->Nn, &nsp));
   HIPCHECK(launch_scalar_combine(N, nsp, c->part, 1.0, c->mtmp, 1.0, c->mq, -0.5, c->mdn, st));
   HIPCHECK(launch_hdot(N, c->Nn, H0[0], H0[1], H0[2], -1.0, 1, c->mdn, st));
   // field and Maxwell traction
@@ -1677,17 +1698,17 @@ extern "C" rbm_status rbm_far_traction(rbm_ctx* c, int n_points, int M, const do
   if (!c->ws) return fail(RBM_E_NOMEM, "bind a workspace first");
   if (n_points < 1 || M < 1) return fail(RBM_E_INVAL, "sizes must be >= 1");
   if (n_points > c->nmax * c->M) return fail(RBM_E_NOMEM, "more points than the workspace holds");
-  const int nsplit = split_for(c, n_points);
+  int nsplit = 0;
   hipStream_t st = c->st;
   const size_t N3 = 3 * (size_t)n_points;
   if (precision == 0) {
-    HIPCHECK(launch_pack_sources<double>(n_points, M, X, nullptr, nullptr, q, 0, nullptr, c->src, st));
-    HIPCHECK(launch_far<double>(0, n_points, M, X, Nrm, c->src, c->part, nsplit, st));
+    HIPCHECK(launch_pack_sources<double>(n_points, M, X, nullptr, nullptr, q, 0, Nrm, c->src, c->nor, st));
+    HIPCHECK(far_sum<double>(c, 0, n_points, M, X, Nrm, &nsplit));
   } else {
     HIPCHECK(launch_cast_f32(N3, X, c->Xf, st));
     HIPCHECK(launch_cast_f32(N3, Nrm, c->Nf, st));
-    HIPCHECK(launch_pack_sources<float>(n_points, M, X, nullptr, nullptr, q, 0, nullptr, c->src, st));
-    HIPCHECK(launch_far<float>(0, n_points, M, c->Xf, c->Nf, c->src, c->part, nsplit, st));
+    HIPCHECK(launch_pack_sources<float>(n_points, M, X, nullptr, nullptr, q, 0, Nrm, c->src, c->nor, st));
+    HIPCHECK(far_sum<float>(c, 0, n_points, M, c->Xf, c->Nf, &nsplit));
   }
   HIPCHECK(launch_combine(n_points, M, nsplit, c->part, 1.0, add, 1.0, nullptr, nullptr, 0.0, y, st));
   c->bodies_dirty = true;  // Xf/Nf were overwritten
@@ -1709,9 +1730,9 @@ extern "C" rbm_status rbm_far_traction_fmm(rbm_ctx* c, int n_points, int M, cons
   if (!c->fmm_ready) return fail(RBM_E_INVAL, "a leaf box would hold more than 4096 points");
   if (level) *level = c->fmm_level;
   if (precision == 0)
-    HIPCHECK(launch_pack_sources<double>(n_points, M, X, nullptr, nullptr, q, 0, nullptr, c->src, c->st));
+    HIPCHECK(launch_pack_sources<double>(n_points, M, X, nullptr, nullptr, q, 0, nullptr, c->src, nullptr, c->st));
   else
-    HIPCHECK(launch_pack_sources<float>(n_points, M, X, nullptr, nullptr, q, 0, nullptr, c->src, c->st));
+    HIPCHECK(launch_pack_sources<float>(n_points, M, X, nullptr, nullptr, q, 0, nullptr, c->src, nullptr, c->st));
   s = fmm_apply(c, precision == 0 ? 0 : 1, y);
   c->fmm_ready = false;  // the tree belongs to these points, not to the bodies
   if (s != RBM_OK) return s;
@@ -1726,16 +1747,16 @@ extern "C" rbm_status rbm_far_stokeslet(rbm_ctx* c, int n_points, int M, const d
   if (!c->ws) return fail(RBM_E_NOMEM, "bind a workspace first");
   if (n_points < 1 || M < 1) return fail(RBM_E_INVAL, "sizes must be >= 1");
   if (n_points > c->nmax * c->M) return fail(RBM_E_NOMEM, "more points than the workspace holds");
-  const int nsplit = split_for(c, n_points);
+  int nsplit = 0;
   hipStream_t st = c->st;
   const size_t N3 = 3 * (size_t)n_points;
   if (precision == 0) {
-    HIPCHECK(launch_pack_sources<double>(n_points, M, X, nullptr, nullptr, q, 0, nullptr, c->src, st));
-    HIPCHECK(launch_far<double>(1, n_points, M, X, nullptr, c->src, c->part, nsplit, st));
+    HIPCHECK(launch_pack_sources<double>(n_points, M, X, nullptr, nullptr, q, 0, nullptr, c->src, nullptr, st));
+    HIPCHECK(far_sum<double>(c, 1, n_points, M, X, nullptr, &nsplit));
   } else {
     HIPCHECK(launch_cast_f32(N3, X, c->Xf, st));
-    HIPCHECK(launch_pack_sources<float>(n_points, M, X, nullptr, nullptr, q, 0, nullptr, c->src, st));
-    HIPCHECK(launch_far<float>(1, n_points, M, c->Xf, nullptr, c->src, c->part, nsplit, st));
+    HIPCHECK(launch_pack_sources<float>(n_points, M, X, nullptr, nullptr, q, 0, nullptr, c->src, nullptr, st));
+    HIPCHECK(far_sum<float>(c, 1, n_points, M, c->Xf, nullptr, &nsplit));
   }
   HIPCHECK(launch_combine(n_points, M, nsplit, c->part, 1.0 / c->opt.eta, nullptr, 0.0, nullptr,
                           nullptr, 0.0, u, st));

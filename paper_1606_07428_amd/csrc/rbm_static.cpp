@@ -21,7 +21,9 @@ using namespace rbm;
 
 namespace {
 
-constexpr size_t kScratchBytes = size_t(64) << 20;  // per GPU
+// Per GPU.  The ordered sum keeps to the first 64 MiB, which also set the largest input; the
+// sums that take every pair once use all of it.
+constexpr size_t kScratchBytes = size_t(192) << 20, kOrderedBytes = size_t(64) << 20;
 constexpr int kMaxDevices = 64;
 
 // Every GPU the library runs on holds its own copy until the process ends.
@@ -68,21 +70,42 @@ extern "C" rbm_status rbm_far_traction_static(int n_points, int M, const double*
   if (n_points < 1 || M < 1) return set_last_error(RBM_E_INVAL, "sizes must be >= 1");
   if (precision != 0 && precision != 1) return set_last_error(RBM_E_INVAL, "precision must be 0 or 1");
   const size_t N = (size_t)n_points;
-  if (scratch_bytes(N, 1, precision) > kScratchBytes)
-    return set_last_error(RBM_E_NOMEM, "more points than the 64 MiB static scratch holds (about 762,000 in "
+  if (scratch_bytes(N, 1, precision) > kOrderedBytes)
+    return set_last_error(RBM_E_NOMEM, "more points than the static scratch takes (about 762,000 in "
                                        "float64, 838,000 in float32)");
-  // the split of the context path, lowered until the partial sums fit
-  int split = far_split(n_points);
-  while (split > 1 && scratch_bytes(N, split, precision) > kScratchBytes) --split;
   unsigned char* base = nullptr;
   rbm_status s = scratch_address(&base);
   if (s != RBM_OK) return s;
-  void* src = base;
-  double* part = reinterpret_cast<double*>(base + align256(N * (precision == 0 ? 64 : 32)));
   hipStream_t st = static_cast<hipStream_t>(stream);
   hipError_t e;
+  // every unordered pair once, as in the context path, where the plan's scratch fits
+  const size_t b_src = align256(N * (precision == 0 ? 64 : 32)), b_nor = align256(N * (precision == 0 ? 32 : 16)),
+               b_out = align256(3 * N * sizeof(double)), front = b_src + b_nor + b_out;
+  if (front < kScratchBytes) {
+    const SymPlan sp = sym_plan(n_points, 0, precision, std::min(sym_cap(N), (kScratchBytes - front) / sizeof(double)));
+    if (sp.rows > 0) {
+      void *src = base, *nor = base + b_src;
+      double* sum = reinterpret_cast<double*>(base + b_src + b_nor);
+      double* part = reinterpret_cast<double*>(base + front);
+      if (precision == 0) {
+        e = launch_pack_sources<double>(n_points, M, X, nullptr, nullptr, q, 0, Nrm, src, nor, st);
+        if (e == hipSuccess) e = launch_far_sym<double>(0, sp, n_points, M, src, nor, part, sum, nullptr, st);
+      } else {
+        e = launch_pack_sources<float>(n_points, M, X, nullptr, nullptr, q, 0, Nrm, src, nor, st);
+        if (e == hipSuccess) e = launch_far_sym<float>(0, sp, n_points, M, src, nor, part, sum, nullptr, st);
+      }
+      if (e == hipSuccess)
+        e = launch_combine(n_points, M, 1, sum, 1.0, add, 1.0, nullptr, nullptr, 0.0, y, st);
+      return e == hipSuccess ? RBM_OK : set_last_error(RBM_E_DEVICE, hipGetErrorString(e));
+    }
+  }
+  // the split of the context path, lowered until the partial sums fit
+  int split = far_split(n_points);
+  while (split > 1 && scratch_bytes(N, split, precision) > kOrderedBytes) --split;
+  void* src = base;
+  double* part = reinterpret_cast<double*>(base + align256(N * (precision == 0 ? 64 : 32)));
   if (precision == 0) {
-    if ((e = launch_pack_sources<double>(n_points, M, X, nullptr, nullptr, q, 0, nullptr, src, st)) != hipSuccess ||
+    if ((e = launch_pack_sources<double>(n_points, M, X, nullptr, nullptr, q, 0, nullptr, src, nullptr, st)) != hipSuccess ||
         (e = launch_far<double>(0, n_points, M, X, Nrm, src, part, split, st)) != hipSuccess)
       return set_last_error(RBM_E_DEVICE, hipGetErrorString(e));
   } else {
@@ -90,7 +113,7 @@ extern "C" rbm_status rbm_far_traction_static(int n_points, int M, const double*
     float* Xf = reinterpret_cast<float*>(f);
     float* Nf = reinterpret_cast<float*>(f + align256(3 * N * sizeof(float)));
     if ((e = launch_cast_f32(3 * N, X, Xf, st)) != hipSuccess || (e = launch_cast_f32(3 * N, Nrm, Nf, st)) != hipSuccess ||
-        (e = launch_pack_sources<float>(n_points, M, X, nullptr, nullptr, q, 0, nullptr, src, st)) != hipSuccess ||
+        (e = launch_pack_sources<float>(n_points, M, X, nullptr, nullptr, q, 0, nullptr, src, nullptr, st)) != hipSuccess ||
         (e = launch_far<float>(0, n_points, M, Xf, Nf, src, part, split, st)) != hipSuccess)
       return set_last_error(RBM_E_DEVICE, hipGetErrorString(e));
   }

@@ -63,3 +63,82 @@ def test_sums_at_small_and_ragged_sizes(n, M, prec):
         return
     tol = 1e-12 if prec == 0 else 1e-5
     assert rel_err(y[idx], rt) < tol and rel_err(u[idx], ru) < tol
+
+
+# Sizes around the rules of the sums that take every unordered pair once: the first size (one
+# block over and exactly full), each class of chunks, phases (the static call at 120,001), the
+# wider blocks, the float32 sums; even and odd numbers of blocks, bodies that span many
+# blocks or none.
+@pytest.mark.parametrize("n,M,prec", [(14999, 312, 0), (15000, 312, 0), (15360, 1, 0), (15361, 16000, 0), (16385, 4000, 0),
+                                      (24576, 312, 0), (28001, 100, 0), (32767, 312, 0), (49999, 544, 0), (50000, 544, 0),
+                                      (35999, 312, 1), (36000, 312, 1), (61441, 5000, 1), (70001, 312, 0), (120001, 312, 0)])
+def test_sums_that_take_every_pair_once(n, M, prec):
+    print(f"\n[case] far sums n={n} M={M} precision={prec}", flush=True)
+    rng, X, Nn, q = _points(n, n + M)
+    add = rng.standard_normal((n, 3))
+    s = _context(n)
+    a = (_dev(X.T), _dev(Nn.T), _dev(q.T))
+    y = s.far_traction(*a, M, add=_dev(add.T), precision=prec)
+    again = s.far_traction(*a, M, add=_dev(add.T), precision=prec)
+    u = s.far_stokeslet(a[0], a[2], M, precision=prec).cpu().numpy().T
+    ys = rbm.far_traction_static(*a, M, add=_dev(add.T), precision=prec).cpu().numpy().T
+    assert torch.equal(y, again)
+    y = y.cpu().numpy().T
+    s.close()
+    if n < 28672:
+        assert np.array_equal(y, ys)
+    if prec:
+        X, Nn, q = (v.astype(np.float32).astype(np.float64) for v in (X, Nn, q))
+    idx = np.unique(np.concatenate([rng.choice(n, 48, replace=False), [0, n - 1, n // 2]]))
+    body = np.arange(n) // M
+    rt = ff.traction_sum(X[idx], Nn[idx], X, q, body[idx], body)
+    ru = ff.stokeslet_sum(X[idx], X, q, body[idx], body)
+    tol = 1e-12 if prec == 0 else 1e-5
+    for got in (y, ys):
+        assert rel_err(got[idx] - add[idx], rt) < tol
+    assert rel_err(u[idx], ru) < tol
+
+
+def test_laplace_sums_that_take_every_pair_once():
+    """phi = -H0 . X + S q and dn = -H0 . n - q/2 + K q of the magnetostatic problem at 18,000
+    points (125 spheres, p = 8): the far parts at sampled targets against the oracle's sums."""
+    from paper_1606_07428_amd import inputs
+    w = inputs.mhd_lattice(side=5, p=8, jitter=0.1, seed=3)
+    s = rbm.solver_for(w, magnetic=1)
+    H0 = np.array([1.0, -2.0, 0.5])
+    s.magnetic_traction(H0, 2.0, tol=1e-10)
+    N, M = s.N, s.M
+    X, Nn = (s.read(k, 3 * N).reshape(3, N).T for k in ("X", "N"))
+    wq, q, phi, dn = (s.read(k, N) for k in ("W", "mag_q", "mag_phi", "mag_dn"))
+    S0, K0 = (s.read(k, M * M).reshape(M, M).T for k in ("SL0", "KL0"))  # column-major
+    s.close()
+    rng = np.random.default_rng(5)
+    body = np.arange(N) // M
+    got, ref = [], []
+    for a in rng.choice(N, 64, replace=False):
+        sl = slice(body[a] * M, (body[a] + 1) * M)
+        keep = body != body[a]
+        d = X[a] - X[keep]
+        r = np.sqrt(np.sum(d * d, axis=1))
+        v = wq[keep] * q[keep]
+        got.append((phi[a] + X[a] @ H0 - S0[a % M] @ q[sl], dn[a] + Nn[a] @ H0 + 0.5 * q[a] - K0[a % M] @ q[sl]))
+        ref.append((np.sum(v / r) / (4 * math.pi), -np.sum((d @ Nn[a]) * v / r**3) / (4 * math.pi)))
+    got, ref = np.array(got), np.array(ref)
+    # the far part is what is left of phi (up to 30 in size here) and dn after the other terms
+    assert np.abs(got[:, 0] - ref[:, 0]).max() < 1e-12 * np.abs(phi).max()
+    assert np.abs(got[:, 1] - ref[:, 1]).max() < 1e-12 * np.abs(dn).max()
+
+
+def test_fused_sum_that_takes_every_pair_once():
+    """200 spheres, p = 12 (62,400 points): the solve whose velocities come from the fused pass
+    against the one that evaluates its Stokeslet sum separately."""
+    from paper_1606_07428_amd import inputs
+    w = inputs.lattice(200, 12)
+    out = []
+    for fusion in (1, 0):
+        s = rbm.solver_for(w, tol=1e-10, velocity_fusion=fusion)
+        VW, info = s.solve(w["FT"])
+        assert info["fused_used"] == fusion
+        out.append(VW)
+        s.close()
+    assert rel_err(out[0], out[1]) < 1e-12
