@@ -37,7 +37,10 @@ hipError_t launch_finish_A0(int ns, int M, const double* gr, const double* gw, d
 hipError_t launch_velocity_functional(int ns, int M, const double* Sop, const double* gr,
                                       const double* gw, const double* shp, double* V0,
                                       hipStream_t st);
-hipError_t launch_gauss_jordan(int ns, int n, double* A, int* piv, hipStream_t st);
+// In-place inverses of ns column-major n x n matrices, n <= 3072 (k_inverse.hip); ints: integer
+// scratch, n + kInverseInts per matrix.
+constexpr int kInverseInts = 260;
+hipError_t launch_invert(int ns, int n, double* A, int* ints, hipStream_t st);
 hipError_t launch_cast_f32(size_t n, const double* x, float* y, hipStream_t st);
 // bf16 stored as raw uint16 (upper half of the fp32 pattern, round to nearest even)
 hipError_t launch_cast_bf16(size_t n, const double* x, uint16_t* y, hipStream_t st);

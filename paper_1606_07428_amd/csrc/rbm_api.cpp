@@ -74,7 +74,7 @@ struct rbm_ctx {
   double *coef, *rcbuf, *gx, *gn, *gw, *gr, *shp, *A0, *P0, *V0;
   float* P0f;
   uint16_t* P0h;
-  int* piv;
+  int* inv_ints;
   // bodies and nodes
   int* sid;
   double *cen, *quat, *FT, *VW, *Rm, *tauinv, *area_b, *mom, *vws;
@@ -338,7 +338,7 @@ static size_t layout(rbm_ctx* c, int nmax, bool assign) {
   take(c->rbc, ns);
   take(c->hsp, ns);
   take(c->A0, ns * M3 * M3); take(c->P0, ns * M3 * M3); take(c->V0, ns * 6 * M3);
-  take(c->piv, ns * M3);
+  take(c->inv_ints, ns * (M3 + kInverseInts));
   if (c->opt.precision == RBM_MIXED_FP32) take(c->P0f, ns * M3 * M3); else if (assign) c->P0f = nullptr;
   if (c->opt.precision == RBM_MIXED_BF16) take(c->P0h, ns * M3 * M3); else if (assign) c->P0h = nullptr;
   const size_t nm = nmax, N = nm * M, N3 = 3 * N;
@@ -486,7 +486,7 @@ extern "C" rbm_status rbm_setup(rbm_ctx* c) {
   HIPCHECK(launch_velocity_functional(c->ns, M, c->P0, c->gr, c->gw, c->shp, c->V0, st));
   HIPCHECK(hipMemcpyAsync(c->P0, c->A0, (size_t)c->ns * M3 * M3 * sizeof(double),
                           hipMemcpyDeviceToDevice, st));
-  HIPCHECK(launch_gauss_jordan(c->ns, M3, c->P0, c->piv, st));
+  HIPCHECK(launch_invert(c->ns, M3, c->P0, c->inv_ints, st));
   if (c->P0f) HIPCHECK(launch_cast_f32((size_t)c->ns * M3 * M3, c->P0, c->P0f, st));
   if (c->P0h) HIPCHECK(launch_cast_bf16((size_t)c->ns * M3 * M3, c->P0, c->P0h, st));
   if (c->opt.magnetic) {
