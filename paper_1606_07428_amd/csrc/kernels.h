@@ -28,11 +28,14 @@ hipError_t launch_shape_geometry(int ns, int p, const double* coef, const double
                                  const double* Yttab, const double* Ypstab, const double* node_lam,
                                  double* gx, double* gn, double* gw, double* gr, double* shp,
                                  hipStream_t st);
-hipError_t launch_singular_assemble(int ns, int p, int ps, double eta, const double* coef,
-                                    const double* gx, const double* gn, const double* node_th,
-                                    const double* node_ph, const double* rnodes, const double* rW,
-                                    const double* Fttab, double* Sop, double* Kop, hipStream_t st);
-hipError_t launch_finish_A0(int ns, int M, const double* gr, const double* gw, double* A0,
+// Singular self operators S, K, row-major per shape (k_singular.hip); tab: scratch of
+// singular_table_doubles(p, ps) doubles.
+size_t singular_table_doubles(int p, int ps);
+hipError_t launch_singular_assemble(int ns, int p, int ps, double eta, const double* coef, const double* gx,
+                                    const double* gn, const double* glr_t, const double* glt, const double* glw,
+                                    const double* rW, double* tab, double* Sop, double* Kop, hipStream_t st);
+// A0 (column-major) = K (row-major) + 1/2 I + L; A0 and K must not overlap
+hipError_t launch_finish_A0(int ns, int M, const double* gr, const double* gw, const double* K, double* A0,
                             hipStream_t st);
 hipError_t launch_velocity_functional(int ns, int M, const double* Sop, const double* gr,
                                       const double* gw, const double* shp, double* V0,

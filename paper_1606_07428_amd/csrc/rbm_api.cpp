@@ -69,7 +69,7 @@ struct rbm_ctx {
   int nblk = 256;
   // tables
   double *gl_t, *gl_w, *glr_t, *glr_w, *Ytab, *Yttab, *Ypstab, *Ftab, *Fttab, *nth, *nph, *nlam,
-      *rnodes, *rW;
+      *rnodes, *rW, *sing_tab;
   // shapes
   double *coef, *rcbuf, *gx, *gn, *gw, *gr, *shp, *A0, *P0, *V0;
   float* P0f;
@@ -331,6 +331,7 @@ static size_t layout(rbm_ctx* c, int nmax, bool assign) {
   take(c->Ftab, (size_t)nB * M); take(c->Fttab, (size_t)nB * M);
   take(c->nth, M); take(c->nph, M); take(c->nlam, M);
   take(c->rnodes, 3 * (size_t)Ms); take(c->rW, Ms);
+  take(c->sing_tab, singular_table_doubles(p, ps));
   take(c->coef, ns * 3 * nc);
   take(c->rcbuf, c->shape_data.size() + 1);
   take(c->gx, ns * 3 * M); take(c->gn, ns * 3 * M); take(c->gr, ns * 3 * M); take(c->gw, ns * M);
@@ -479,11 +480,11 @@ extern "C" rbm_status rbm_setup(rbm_ctx* c) {
   }
   HIPCHECK(launch_shape_geometry(c->ns, p, c->coef, c->Ytab, c->Yttab, c->Ypstab, c->nlam, c->gx,
                                  c->gn, c->gw, c->gr, c->shp, st));
-  // S0 into the P0 buffer (temporary), K0 into A0
-  HIPCHECK(launch_singular_assemble(c->ns, p, c->ps, c->opt.eta, c->coef, c->gx, c->gn, c->nth,
-                                    c->nph, c->rnodes, c->rW, c->Fttab, c->P0, c->A0, st));
-  HIPCHECK(launch_finish_A0(c->ns, M, c->gr, c->gw, c->A0, st));
-  HIPCHECK(launch_velocity_functional(c->ns, M, c->P0, c->gr, c->gw, c->shp, c->V0, st));
+  // S0 into the A0 buffer and K0 into P0, both row-major and temporary
+  HIPCHECK(launch_singular_assemble(c->ns, p, c->ps, c->opt.eta, c->coef, c->gx, c->gn, c->glr_t, c->gl_t, c->gl_w,
+                                    c->rW, c->sing_tab, c->A0, c->P0, st));
+  HIPCHECK(launch_velocity_functional(c->ns, M, c->A0, c->gr, c->gw, c->shp, c->V0, st));
+  HIPCHECK(launch_finish_A0(c->ns, M, c->gr, c->gw, c->P0, c->A0, st));
   HIPCHECK(hipMemcpyAsync(c->P0, c->A0, (size_t)c->ns * M3 * M3 * sizeof(double),
                           hipMemcpyDeviceToDevice, st));
   HIPCHECK(launch_invert(c->ns, M3, c->P0, c->inv_ints, st));
