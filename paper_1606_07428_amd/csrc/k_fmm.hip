@@ -24,6 +24,8 @@
 // the same or adjacent leaves: every same-body pair falls in the direct near field,
 // where it is skipped; none goes through an expansion.  Near field: the 27 adjacent
 // leaves.  Interaction lists at levels 2..L: boxes not adjacent whose parents are.
+#include <type_traits>
+
 #include "common.h"
 #include "kernels.h"
 #include "pair.h"
@@ -33,6 +35,7 @@ namespace rbm {
 constexpr int kFmmPMax = kFmmMaxOrder;
 constexpr int kFmmKc = (kFmmPMax + 1) * (kFmmPMax + 2) / 2;          // coefficients, m >= 0
 constexpr int kFmmLeafMax = kFmmLeafCap;                              // points per leaf
+constexpr int kFmmLeafWaves = 16;                                      // waves per leaf work item, at most
 constexpr int kFmmVecs = 343;                                         // displacements in [-3, 3]^3
 
 template <typename T> struct Cx { T re, im; };
@@ -569,34 +572,45 @@ __global__ void k_fmm_task_fill(int nbox, const int* __restrict__ tcnt, const in
   for (int j = 0; j < tcnt[b]; ++j) task[toff[b] + j] = make_int2(b, 64 * j);
 }
 
-// Sources in leaf order: srt[p] = src[perm[p]] with the body index in v[6].
+// Sources in leaf order: srt[p] = src[perm[p]] with the body index in v[6] and, in v[7], the
+// body index that the four points from p on share, or -1.
 template <typename T>
 __global__ void k_fmm_pack_sorted(int N, const int* __restrict__ perm, const double4* __restrict__ Xs,
                                   const Src8<T>* __restrict__ src, Src8<T>* __restrict__ srt) {
   const int p = blockIdx.x * blockDim.x + threadIdx.x;
   if (p >= N) return;
   Src8<T> s = src[perm[p]];
-  s.v[6] = (T)Xs[p].w;
-  s.v[7] = 0;
+  const double body = Xs[p].w;
+  bool one = p + 3 < N;
+  for (int k = 1; k < 4; ++k) one = one && Xs[min(p + k, N - 1)].w == body;
+  s.v[6] = (T)body;
+  s.v[7] = one ? (T)body : T(-1);
   srt[p] = s;
 }
 
-// Leaf evaluation, one wave per work item (64 targets of one leaf, one per lane): far field
+// Leaf evaluation, one workgroup per work item (64 targets of one leaf, one per lane): far field
 // from the leaf's local expansions, plus the direct traction sum over the points of the 27
 // adjacent leaves that belong to other bodies.  The leaf is wave-uniform, so its expansion
 // coefficients and the sources (9 contiguous ranges of the leaf-ordered points) are read
 // with scalar loads.  Writes -(3/4pi)-scaled sums to out[3][N] at the original indices.
+// The workgroup's waves take equal parts of the sources (the first, which also evaluates the
+// expansions, as many fewer as that costs) and add their sums through LDS, in order: with a wave
+// per work item the last wave of a CU ran alone for up to a third of the time, and small trees
+// left SIMDs without one.
+// Bound: the vector units, 21 operations a pair (26 with the mask of the same body's pairs on every
+// pair).  1,248,000 points in 4096 leaves (9.3e9 pairs), float32: 5.68 -> 5.10 ms; the whole
+// far_traction_fmm of 142,877 points 3.20 -> 2.62 ms.
 template <typename T>
-__global__ void __launch_bounds__(256) k_fmm_leaf(int P, int nb, double lox, double loy, double loz, double w,
-                                                  int N, int ntask, const int2* __restrict__ task,
+__global__ void __launch_bounds__(1024) k_fmm_leaf(int P, int nb, double lox, double loy, double loz, double w,
+                                                  int N, const int2* __restrict__ task,
                                                   const int* __restrict__ start, const int* __restrict__ perm,
                                                   const double4* __restrict__ Xs, const double4* __restrict__ Ns,
                                                   const Src8<T>* __restrict__ srt, const Cx<T>* __restrict__ Lleaf,
                                                   int far_on, double* __restrict__ out) {
-  const int wv = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6));
-  if (wv >= ntask) return;
+  __shared__ T sum[kFmmLeafWaves - 1][3][64];
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), nw = blockDim.x >> 6;
   const int lane = threadIdx.x & 63;
-  const int2 tk = task[wv];
+  const int2 tk = task[blockIdx.x];
   const int b = __builtin_amdgcn_readfirstlane(tk.x), t0 = __builtin_amdgcn_readfirstlane(tk.y);
   const int s0 = start[b], nt = start[b + 1] - s0;
   const int t = t0 + lane;
@@ -608,7 +622,7 @@ __global__ void __launch_bounds__(256) k_fmm_leaf(int P, int nb, double lox, dou
   const T xa = (T)xt.x, ya = (T)xt.y, za = (T)xt.z, nx = (T)nn.x, ny = (T)nn.y, nz = (T)nn.z;
   const T bt = (T)xt.w;
   T fx = 0, fy = 0, fz = 0;
-  if (far_on) {
+  if (far_on && wv == 0) {
     const Cx<T>* Lb = Lleaf + (size_t)b * 4 * Kc;
     const T ssx = (T)(xt.x - cx), ssy = (T)(xt.y - cy), ssz = (T)(xt.z - cz);
     const T r2 = ssx * ssx + ssy * ssy + ssz * ssz;
@@ -668,38 +682,84 @@ __global__ void __launch_bounds__(256) k_fmm_leaf(int P, int nb, double lox, dou
     fy = sc * (div * ny + Hs[3] * nx + Hs[1] * ny + Hs[5] * nz);
     fz = sc * (div * nz + Hs[4] * nx + Hs[5] * ny + Hs[2] * nz);
   }
-  // near field: traction of the other bodies' points in the 27 adjacent leaves
-  // (same-body pairs: weight 0, and |d|^2 + 1 keeps the point's own pair finite; the
-  // arithmetic mask keeps the loop free of branches)
-  auto near = [&](const Src8<T>& s) {
+  // near field: traction of the other bodies' points in the 27 adjacent leaves.  Four sources per
+  // step, their scalar loads issued a step ahead; if they are points of one body that no lane's
+  // target belongs to, which is nearly always so, the pairs need no mask.  Otherwise
+  // same-body pairs get weight 0, and |d|^2 + 1 keeps the point's own pair finite.
+  auto near = [&](const Src8<T>& s, auto masked) {
     const T dx = xa - s.v[0], dy = ya - s.v[1], dz = za - s.v[2];
-    const T other = s.v[6] == bt ? T(0) : T(1);
-    const T r2 = fma(dx, dx, fma(dy, dy, fma(dz, dz, T(1) - other)));
+    T r2 = fma(dx, dx, fma(dy, dy, dz * dz));
     const T dn = dx * nx + dy * ny + dz * nz;
     const T dq = dx * s.v[3] + dy * s.v[4] + dz * s.v[5];
-    const T f = ((dn * dq) * other) * rinv5_t(r2);
+    T c = dn * dq;
+    if (decltype(masked)::value && s.v[6] == bt) {
+      r2 += T(1);
+      c = T(0);
+    }
+    const T f = c * rinv5_t(r2);
     fx += f * dx;
     fy += f * dy;
     fz += f * dz;
   };
   // for each (nk, nj) the leaves ni - 1 .. ni + 1 are consecutive in leaf order
   const int i0 = max(0, i - 1), i1 = min(nb - 1, i + 1);
-  for (int nk = max(0, k - 1); nk <= min(nb - 1, k + 1); ++nk)
-    for (int nj = max(0, j - 1); nj <= min(nb - 1, j + 1); ++nj) {
+  const int k0 = max(0, k - 1), k1 = min(nb - 1, k + 1), j0 = max(0, j - 1), j1 = min(nb - 1, j + 1);
+  int total = 0;
+  for (int nk = k0; nk <= k1; ++nk)
+    for (int nj = j0; nj <= j1; ++nj) {
+      const int row = (nk * nb + nj) * nb;
+      total += start[row + i1 + 1] - start[row + i0];
+    }
+  // this wave's part [from, to) of the concatenated ranges; the expansions cost about as much as
+  // 5 P^2 / 2 sources
+  const int far = far_on ? 5 * P * P / 2 : 0, each = (total + far + nw - 1) / nw;
+  const int from = __builtin_amdgcn_readfirstlane(max(0, wv * each - far));
+  const int to = __builtin_amdgcn_readfirstlane(min(total, max(0, (wv + 1) * each - far)));
+  int before = 0;
+  for (int nk = k0; nk <= k1; ++nk)
+    for (int nj = j0; nj <= j1; ++nj) {
       const int row = (nk * nb + nj) * nb;
       const int a0 = __builtin_amdgcn_readfirstlane(start[row + i0]);
       const int a1 = __builtin_amdgcn_readfirstlane(start[row + i1 + 1]);
-      // four sources per step: their scalar loads are issued together
-      int q = a0;
-      for (; q + 4 <= a1; q += 4) {
-        const Src8<T> s0 = srt[q], s1 = srt[q + 1], s2 = srt[q + 2], s3 = srt[q + 3];
-        near(s0);
-        near(s1);
-        near(s2);
-        near(s3);
+      int q = a0 + max(0, from - before);
+      const int e = min(a1, a0 + (to - before));
+      before += a1 - a0;
+      if (q + 4 <= e) {
+        Src8<T> n0 = srt[q], n1 = srt[q + 1], n2 = srt[q + 2], n3 = srt[q + 3];
+        for (; q + 4 <= e; q += 4) {
+          const Src8<T> s0 = n0, s1 = n1, s2 = n2, s3 = n3;
+          const int nq = min(q + 4, e - 4);
+          n0 = srt[nq];
+          n1 = srt[nq + 1];
+          n2 = srt[nq + 2];
+          n3 = srt[nq + 3];
+          if (!__any(s0.v[7] < T(0) || s0.v[7] == bt)) {
+            near(s0, std::false_type{});
+            near(s1, std::false_type{});
+            near(s2, std::false_type{});
+            near(s3, std::false_type{});
+          } else {
+            near(s0, std::true_type{});
+            near(s1, std::true_type{});
+            near(s2, std::true_type{});
+            near(s3, std::true_type{});
+          }
+        }
       }
-      for (; q < a1; ++q) near(srt[q]);
+      for (; q < e; ++q) near(srt[q], std::true_type{});
     }
+  if (wv > 0) {
+    sum[wv - 1][0][lane] = fx;
+    sum[wv - 1][1][lane] = fy;
+    sum[wv - 1][2][lane] = fz;
+  }
+  __syncthreads();
+  if (wv > 0) return;
+  for (int v = 0; v < nw - 1; ++v) {
+    fx += sum[v][0][lane];
+    fy += sum[v][1][lane];
+    fz += sum[v][2][lane];
+  }
   if (live) {
     const int g = perm[s0 + t];
     const double sc = -3.0 / (4.0 * RBM_PI);
@@ -805,8 +865,11 @@ hipError_t launch_fmm_apply(int P, int L, const double* lo, double D, int N, con
                                                 Lx + lev_off[lev - 1] * 4 * Kc, Lx + lev_off[lev] * 4 * Kc);
     }
   }
+  // waves per work item: 4 where the items alone give every SIMD some (4096 items are 16 waves a
+  // SIMD), more below
+  const int nw = ntask >= 4096 ? 4 : ntask >= 2048 ? 8 : kFmmLeafWaves;
   if (ntask > 0)
-    k_fmm_leaf<T><<<(ntask + 3) / 4, 256, 0, st>>>(P, nb, lo[0], lo[1], lo[2], w, N, ntask, task, start, perm, Xs,
+    k_fmm_leaf<T><<<ntask, 64 * nw, 0, st>>>(P, nb, lo[0], lo[1], lo[2], w, N, task, start, perm, Xs,
                                                    Ns, so, far_on ? Lx + lev_off[L] * 4 * Kc : nullptr,
                                                    far_on ? 1 : 0, out);
   return hipGetLastError();
