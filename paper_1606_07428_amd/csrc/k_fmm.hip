@@ -27,6 +27,7 @@
 #include <type_traits>
 
 #include "common.h"
+#include "fmm.h"
 #include "kernels.h"
 #include "pair.h"
 
@@ -38,15 +39,11 @@ constexpr int kFmmLeafMax = kFmmLeafCap;                              // points 
 constexpr int kFmmLeafWaves = 16;                                      // waves per leaf work item, at most
 constexpr int kFmmVecs = 343;                                         // displacements in [-3, 3]^3
 
-template <typename T> struct Cx { T re, im; };
-
 template <typename T>
 __device__ __forceinline__ void cfma(Cx<T>& acc, Cx<T> a, Cx<T> b) {
   acc.re = fma(a.re, b.re, fma(-a.im, b.im, acc.re));
   acc.im = fma(a.re, b.im, fma(a.im, b.re, acc.im));
 }
-
-__host__ __device__ __forceinline__ int tri(int n, int m) { return n * (n + 1) / 2 + m; }
 
 // Entry (n, m) of a half table, any sign of m: X_n^{-m} = (-1)^m conj(X_n^m).
 template <typename T>
@@ -252,10 +249,10 @@ __global__ void k_fmm_level_count(int np, const int* __restrict__ cc, int* __res
 //   tabI[lev][v] = I(v w) for v in [-3, 3]^3 with max |v_i| >= 2 (M2L), degree 2P, all m
 //   ((2P + 1)^2 entries, n^2 + n + m).
 template <typename T>
-__global__ void k_fmm_tables(int P, int L, double D, Cx<T>* __restrict__ tabR, Cx<T>* __restrict__ tabI) {
+__global__ void k_fmm_tables(int P, int L, double D, int nv, Cx<T>* __restrict__ tabR, Cx<T>* __restrict__ tabI) {
   const int lev = 2 + blockIdx.y;
   const int e = blockIdx.x * blockDim.x + threadIdx.x;
-  if (lev > L || e >= 8 + kFmmVecs) return;
+  if (lev > L || e >= 8 + nv) return;
   const int Kc = tri(P + 1, 0), F2 = (2 * P + 1) * (2 * P + 1);
   const double w = ldexp(D, -lev);
   if (e < 8) {
@@ -423,14 +420,7 @@ __global__ void __launch_bounds__(1024) k_fmm_m2m(int P, int nc, double wc, cons
 // displacement (all m) is staged in LDS.  The psi shift from the source centre to the
 // target's (- a . phi) is applied after the translation, by linearity:
 // T(psi - a.phi) = T(psi) - a . T(phi).  The parents' locals are added afterwards (L2L).
-// Per level: points per box, first box in the expansion arrays, first workgroup of the
-// level in the fused M2L launch (levels 2..L, ascending).
-struct FmmLevels {
-  const int* cnt[8];
-  size_t off[8];
-  int first[9];
-};
-
+// Float64, and float32 above order kFmmRotOrder; otherwise k_fmm_m2l_rot takes its place.
 template <typename T>
 __global__ void __launch_bounds__(256) k_fmm_m2l(int P, int L, double D, FmmLevels lv,
                                                  const Cx<T>* __restrict__ tabI, const Cx<T>* __restrict__ Mexp,
@@ -811,11 +801,17 @@ static int fmm_threads(int P) {
   return (o + 63) / 64 * 64;
 }
 
+// Translations by rotation or dense.  At order 12 and 4096 leaves the dense kernel takes 5.1 ms, the
+// rotations 1.52; they have float32 tables, and two tiles of 8 orders each.
+template <typename T>
+static constexpr bool fmm_rotates(int P) { return sizeof(T) == 4 && P <= kFmmRotOrder; }
+
 template <typename T>
 hipError_t launch_fmm_tables(int P, int L, double D, void* tabR, void* tabI, hipStream_t st) {
   if (P < 2 || P > kFmmPMax || L < 2) return hipErrorInvalidValue;
-  dim3 grid((8 + kFmmVecs + 63) / 64, L - 1);
-  k_fmm_tables<T><<<grid, 64, 0, st>>>(P, L, D, static_cast<Cx<T>*>(tabR), static_cast<Cx<T>*>(tabI));
+  const int nv = fmm_rotates<T>(P) ? 0 : kFmmVecs;
+  dim3 grid((8 + nv + 63) / 64, L - 1);
+  k_fmm_tables<T><<<grid, 64, 0, st>>>(P, L, D, nv, static_cast<Cx<T>*>(tabR), static_cast<Cx<T>*>(tabI));
   return hipGetLastError();
 }
 
@@ -825,8 +821,9 @@ hipError_t launch_fmm_tables(int P, int L, double D, void* tabR, void* tabI, hip
 template <typename T>
 hipError_t launch_fmm_apply(int P, int L, const double* lo, double D, int N, const int* start, const int* perm,
                             const double4* Xs, const double4* Ns, int* const* cnt_lev, const size_t* lev_off,
-                            int ntask, const int2* task, const void* tabR, const void* tabI, const void* src,
-                            void* srt, void* Mexp, void* Lexp, double* out, hipStream_t st) {
+                            int ntask, const int2* task, const void* tabR, const void* tabI, int max_level,
+                            const float* rot, const void* src, void* srt, void* Mexp, void* Lexp, double* out,
+                            hipStream_t st) {
   if (P < 2 || P > kFmmPMax || L < 0) return hipErrorInvalidValue;
   const int nb = 1 << L, Kc = tri(P + 1, 0);
   const double w = ldexp(D, -L);
@@ -858,7 +855,15 @@ hipError_t launch_fmm_apply(int P, int L, const double* lo, double D, int N, con
     }
     lv.first[L + 1] = nwg;
     const int thl = (Kc + 63) / 64 * 64;
-    k_fmm_m2l<T><<<nwg, thl, 0, st>>>(P, L, D, lv, tI, Mx, Lx);
+    bool done = false;
+    if constexpr (sizeof(T) == 4) {
+      if (fmm_rotates<T>(P)) {
+        const hipError_t e = launch_fmm_m2l_rot(P, L, max_level, D, lv, rot, Mx, Lx, st);
+        if (e != hipSuccess) return e;
+        done = true;
+      }
+    }
+    if (!done) k_fmm_m2l<T><<<nwg, thl, 0, st>>>(P, L, D, lv, tI, Mx, Lx);
     for (int lev = 3; lev <= L; ++lev) {
       const int nl = 1 << lev;
       k_fmm_l2l<T><<<nl * nl * nl, thl, 0, st>>>(P, nl, ldexp(D, -lev), cnt_lev[lev], tR + (size_t)(lev - 2) * 8 * Kc,
@@ -879,11 +884,11 @@ template hipError_t launch_fmm_tables<double>(int, int, double, void*, void*, hi
 template hipError_t launch_fmm_tables<float>(int, int, double, void*, void*, hipStream_t);
 template hipError_t launch_fmm_apply<double>(int, int, const double*, double, int, const int*, const int*,
                                              const double4*, const double4*, int* const*, const size_t*, int,
-                                             const int2*, const void*, const void*, const void*, void*, void*,
-                                             void*, double*, hipStream_t);
+                                             const int2*, const void*, const void*, int, const float*,
+                                             const void*, void*, void*, void*, double*, hipStream_t);
 template hipError_t launch_fmm_apply<float>(int, int, const double*, double, int, const int*, const int*,
                                             const double4*, const double4*, int* const*, const size_t*, int,
-                                            const int2*, const void*, const void*, const void*, void*, void*,
-                                            void*, double*, hipStream_t);
+                                            const int2*, const void*, const void*, int, const float*, const void*,
+                                            void*, void*, void*, double*, hipStream_t);
 
 }  // namespace rbm

@@ -225,8 +225,9 @@ hipError_t launch_fmm_tables(int P, int L, double D, void* tabR, void* tabI, hip
 template <typename T>
 hipError_t launch_fmm_apply(int P, int L, const double* lo, double D, int N, const int* start, const int* perm,
                             const double4* Xs, const double4* Ns, int* const* cnt_lev, const size_t* lev_off,
-                            int ntask, const int2* task, const void* tabR, const void* tabI, const void* src,
-                            void* srt, void* Mexp, void* Lexp, double* out, hipStream_t st);
+                            int ntask, const int2* task, const void* tabR, const void* tabI, int max_level,
+                            const float* rot, const void* src, void* srt, void* Mexp, void* Lexp, double* out,
+                            hipStream_t st);
 
 // ---- magnetostatics (k_magnetic.hip) -------------------------------------------------
 // Laplace self operators S^L, K^L per shape, column-major [ns][M][M] (singular rule)

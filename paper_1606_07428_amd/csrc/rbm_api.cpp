@@ -18,6 +18,7 @@
 #include "../../include/rbm.h"
 #include "kernels.h"
 #include "far_plan.h"
+#include "fmm.h"
 
 using namespace rbm;
 
@@ -118,6 +119,7 @@ struct rbm_ctx {
   double4 *fXs = nullptr, *fNs = nullptr;
   double* fbounds = nullptr;
   void *ftabR = nullptr, *ftabI = nullptr, *fM = nullptr, *fL = nullptr;
+  float* frot = nullptr;
   bool fmm_ready = false;
   int fmm_level = 0, fmm_npts = 0;
   double fmm_lo[3] = {0, 0, 0}, fmm_D = 1.0;
@@ -393,6 +395,7 @@ static size_t layout(rbm_ctx* c, int nmax, bool assign) {
     double *tr = nullptr, *ti = nullptr, *me = nullptr, *le = nullptr;
     take(tr, 2 * (size_t)(Lm - 1) * 8 * kc); take(ti, 2 * (size_t)(Lm - 1) * 343 * kc2);
     take(me, 2 * btot * 4 * kc); take(le, 2 * btot * 4 * kc);
+    if (P <= kFmmRotOrder) take(c->frot, fmm_rotation_floats(Lm)); else if (assign) c->frot = nullptr;
     if (assign) {
       c->ftabR = tr;
       c->ftabI = ti;
@@ -748,6 +751,8 @@ static rbm_status fmm_build(rbm_ctx* c, int npts, int M, const double* X, const 
   HIPCHECK(hipMemcpyAsync(c->pinned, c->ftoff + ((size_t)1 << (3 * L)), sizeof(int), hipMemcpyDeviceToHost, st));
   HIPCHECK(hipStreamSynchronize(st));
   std::memcpy(&c->fmm_ntask, c->pinned, sizeof(int));
+  if (L >= 2 && c->opt.fmm_order <= kFmmRotOrder)
+    HIPCHECK(launch_fmm_rotations(c->opt.fmm_order, L, c->opt.fmm_max_level, c->fmm_D, c->frot, st));
   c->fmm_npts = npts;
   c->fmm_ready = true;
   return RBM_OK;
@@ -768,12 +773,12 @@ static rbm_status fmm_apply(rbm_ctx* c, int prec, double* out) {
     if (L >= 2) HIPCHECK(launch_fmm_tables<double>(P, L, c->fmm_D, c->ftabR, c->ftabI, c->st));
     HIPCHECK(launch_fmm_apply<double>(P, L, c->fmm_lo, c->fmm_D, c->fmm_npts, c->fstart, c->fperm, c->fXs,
                                       c->fNs, c->fmm_cnt, c->fmm_off, c->fmm_ntask, c->ftask, c->ftabR, c->ftabI,
-                                      c->src, c->fsrt, c->fM, c->fL, out, c->st));
+                                      c->opt.fmm_max_level, c->frot, c->src, c->fsrt, c->fM, c->fL, out, c->st));
   } else {
     if (L >= 2) HIPCHECK(launch_fmm_tables<float>(P, L, c->fmm_D, c->ftabR, c->ftabI, c->st));
     HIPCHECK(launch_fmm_apply<float>(P, L, c->fmm_lo, c->fmm_D, c->fmm_npts, c->fstart, c->fperm, c->fXs,
                                      c->fNs, c->fmm_cnt, c->fmm_off, c->fmm_ntask, c->ftask, c->ftabR, c->ftabI,
-                                     c->src, c->fsrt, c->fM, c->fL, out, c->st));
+                                     c->opt.fmm_max_level, c->frot, c->src, c->fsrt, c->fM, c->fL, out, c->st));
   }
   return RBM_OK;
 }
