@@ -24,6 +24,7 @@
 // the same or adjacent leaves: every same-body pair falls in the direct near field,
 // where it is skipped; none goes through an expansion.  Near field: the 27 adjacent
 // leaves.  Interaction lists at levels 2..L: boxes not adjacent whose parents are.
+#include <algorithm>
 #include <type_traits>
 
 #include "common.h"
@@ -120,26 +121,49 @@ __device__ void irregular_table(int Q, double x, double y, double z, Cx<T>* out)
 // ---------------------------------------------------------------------------------
 // Tree construction (float64 coordinates)
 
-// Componentwise min and max of X ([3][N]) into out[6] (one workgroup).
-__global__ void __launch_bounds__(1024) k_fmm_bounds(int N, const double* __restrict__ X, double* out) {
-  __shared__ double red[6][1024];
+// Componentwise min and max of this workgroup's share of X ([3][N], first = true), or of earlier
+// results X ([N][6]), into out[6 blockIdx.x ..].  Bound: HBM; one workgroup for all points read at 55
+// GB/s (1,248,000 points: 0.55 ms, two launches over the chip 0.014).
+template <bool FIRST>
+__global__ void __launch_bounds__(256) k_fmm_bounds(int N, const double* __restrict__ X, double* out) {
+  __shared__ double red[6][256];
   double v[6] = {1e300, 1e300, 1e300, -1e300, -1e300, -1e300};
-  for (int i = threadIdx.x; i < N; i += blockDim.x)
+  for (int i = blockIdx.x * 256 + threadIdx.x; i < N; i += gridDim.x * 256)
     for (int d = 0; d < 3; ++d) {
-      const double x = X[(size_t)d * N + i];
-      v[d] = fmin(v[d], x);
-      v[3 + d] = fmax(v[3 + d], x);
+      v[d] = fmin(v[d], FIRST ? X[(size_t)d * N + i] : X[6 * i + d]);
+      v[3 + d] = fmax(v[3 + d], FIRST ? X[(size_t)d * N + i] : X[6 * i + 3 + d]);
     }
   for (int d = 0; d < 6; ++d) red[d][threadIdx.x] = v[d];
   __syncthreads();
-  for (int s = blockDim.x / 2; s > 0; s >>= 1) {
+  for (int s = 128; s > 0; s >>= 1) {
     if ((int)threadIdx.x < s)
       for (int d = 0; d < 6; ++d)
         red[d][threadIdx.x] = d < 3 ? fmin(red[d][threadIdx.x], red[d][threadIdx.x + s])
                                     : fmax(red[d][threadIdx.x], red[d][threadIdx.x + s]);
     __syncthreads();
   }
-  if (threadIdx.x < 6) out[threadIdx.x] = red[threadIdx.x][0];
+  if (threadIdx.x < 6) out[6 * blockIdx.x + threadIdx.x] = red[threadIdx.x][0];
+}
+
+// counter[key] += 1 for the active lanes of a wave; every lane's old value (the order among lanes of one
+// key is that of the lanes).  Consecutive points are a body's, which lies in a few leaves: one
+// addition for all lanes of a key, for the first four keys; atomics of single lanes on one address
+// run one after the other (1,248,000 points: counting 0.27 -> 0.010 ms, scattering 0.36 -> 0.010).
+__device__ __forceinline__ int wave_count(int key, bool active, int* counter) {
+  unsigned long long todo = __ballot(active);
+  const int lane = threadIdx.x & 63;
+  int pos = 0;
+  for (int r = 0; r < 4 && todo; ++r) {
+    const int leader = __ffsll(todo) - 1, k = __builtin_amdgcn_readlane(key, leader);
+    const unsigned long long same = __ballot(key == k) & todo;
+    int base = 0;
+    if (lane == leader) base = atomicAdd(counter + k, __popcll(same));
+    base = __builtin_amdgcn_readlane(base, leader);
+    if (same >> lane & 1) pos = base + __popcll(same & ((1ull << lane) - 1));
+    todo &= ~same;
+  }
+  if (todo >> lane & 1) pos = atomicAdd(counter + key, 1);
+  return pos;
 }
 
 __device__ __forceinline__ int leaf_coord(double x, double lo, double w, int nb) {
@@ -150,13 +174,16 @@ __device__ __forceinline__ int leaf_coord(double x, double lo, double w, int nb)
 __global__ void k_fmm_count(int N, const double* __restrict__ X, double lox, double loy, double loz,
                             double w, int nb, int* __restrict__ leaf, int* __restrict__ cnt) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= N) return;
-  const int a = leaf_coord(X[i], lox, w, nb);
-  const int b = leaf_coord(X[(size_t)N + i], loy, w, nb);
-  const int c = leaf_coord(X[2 * (size_t)N + i], loz, w, nb);
-  const int id = (c * nb + b) * nb + a;
-  leaf[i] = id;
-  atomicAdd(cnt + id, 1);
+  const bool live = i < N;
+  int id = 0;
+  if (live) {
+    const int a = leaf_coord(X[i], lox, w, nb);
+    const int b = leaf_coord(X[(size_t)N + i], loy, w, nb);
+    const int c = leaf_coord(X[2 * (size_t)N + i], loz, w, nb);
+    id = (c * nb + b) * nb + a;
+    leaf[i] = id;
+  }
+  wave_count(id, live, cnt);
 }
 
 // Exclusive scan of cnt[0, nbox) into start[0, nbox]; largest count to *maxcnt.
@@ -196,9 +223,10 @@ __global__ void __launch_bounds__(1024) k_fmm_scan(int nbox, const int* __restri
 __global__ void k_fmm_scatter(int N, const int* __restrict__ leaf, const int* __restrict__ start,
                               int* __restrict__ fill, int* __restrict__ perm) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= N) return;
-  const int b = leaf[i];
-  perm[start[b] + atomicAdd(fill + b, 1)] = i;
+  const bool live = i < N;
+  const int b = live ? leaf[i] : 0;
+  const int at = wave_count(b, live, fill);
+  if (live) perm[start[b] + at] = i;
 }
 
 // Order every leaf's segment of perm by point index (the atomic scatter leaves it in
@@ -762,8 +790,14 @@ __global__ void __launch_bounds__(1024) k_fmm_leaf(int P, int nb, double lox, do
 // ---------------------------------------------------------------------------------
 // Launchers
 
-hipError_t launch_fmm_bounds(int N, const double* X, double* out6, hipStream_t st) {
-  k_fmm_bounds<<<1, 1024, 0, st>>>(N, X, out6);
+hipError_t launch_fmm_bounds(int N, const double* X, double* scratch, double* out6, hipStream_t st) {
+  const int nwg = std::min(512, (N + 1023) / 1024);
+  if (nwg == 1) {
+    k_fmm_bounds<true><<<1, 256, 0, st>>>(N, X, out6);
+  } else {
+    k_fmm_bounds<true><<<nwg, 256, 0, st>>>(N, X, scratch);
+    k_fmm_bounds<false><<<1, 256, 0, st>>>(nwg, scratch, out6);
+  }
   return hipGetLastError();
 }
 

@@ -213,7 +213,8 @@ hipError_t launch_bound_radius(int ns, int M, const double* r, double* rb, hipSt
 // usable when no leaf holds more than kFmmLeafCap points.
 constexpr int kFmmMaxOrder = 16;
 constexpr int kFmmLeafCap = 4096;
-hipError_t launch_fmm_bounds(int N, const double* X, double* out6, hipStream_t st);
+// scratch: 6 doubles per 1024 points
+hipError_t launch_fmm_bounds(int N, const double* X, double* scratch, double* out6, hipStream_t st);
 hipError_t launch_fmm_sort_points(int N, int M, const double* X, const double* Nn, const double* lo, double w,
                                   int nb, int* leaf, int* cnt, int* start, int* fill, int* perm, int* maxcnt,
                                   double4* Xs, double4* Ns, hipStream_t st);

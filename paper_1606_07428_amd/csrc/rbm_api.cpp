@@ -713,7 +713,7 @@ static rbm_status near_correction(rbm_ctx* c, SolveState& S, int kind, const dou
 static rbm_status fmm_build(rbm_ctx* c, int npts, int M, const double* X, const double* Nn, double d_max) {
   c->fmm_ready = false;
   hipStream_t st = c->st;
-  HIPCHECK(launch_fmm_bounds(npts, X, c->fbounds, st));
+  HIPCHECK(launch_fmm_bounds(npts, X, c->fsrt, c->fbounds, st));
   HIPCHECK(hipMemcpyAsync(c->pinned, c->fbounds, 6 * sizeof(double), hipMemcpyDeviceToHost, st));
   HIPCHECK(hipStreamSynchronize(st));
   double e = 0.0;
