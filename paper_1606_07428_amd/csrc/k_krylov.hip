@@ -8,44 +8,44 @@
 
 namespace rbm {
 
-// partial[j*nblk + blk] = sum over the block's slice of V[j] . w, j < kk
-__global__ __launch_bounds__(256) void k_dots(int kk, size_t len, const double* __restrict__ V,
-                                              size_t ldv, const double* __restrict__ w,
-                                              double* __restrict__ partial, int nblk) {
+// partial[blk] = the block's part of w . w
+__global__ __launch_bounds__(256) void k_norm_parts(size_t len, const double* __restrict__ w,
+                                                    double* __restrict__ partial, int nblk) {
   __shared__ double red[4];
   const size_t stride = (size_t)nblk * 256;
-  for (int j = 0; j < kk; ++j) {
-    const double* v = V + (size_t)j * ldv;
-    double acc = 0.0;
-    for (size_t e = (size_t)blockIdx.x * 256 + threadIdx.x; e < len; e += stride) acc += v[e] * w[e];
-    const double s = block_sum(acc, red);
-    if (threadIdx.x == 0) partial[(size_t)j * nblk + blockIdx.x] = s;
-  }
-}
-
-hipError_t launch_dots(int kk, size_t len, const double* V, size_t ldv, const double* w,
-                       double* partial, int nblk, hipStream_t st) {
-  k_dots<<<nblk, 256, 0, st>>>(kk, len, V, ldv, w, partial, nblk);
-  return hipGetLastError();
-}
-
-// h[j] = sum_blk partial (fixed order); optional hacc[j] += h[j]; take_sqrt -> h = sqrt(h)
-__global__ __launch_bounds__(256) void k_dots_final(int nblk, const double* partial, double* h,
-                                                    double* hacc, int take_sqrt) {
-  __shared__ double red[4];
-  const int j = blockIdx.x;
   double acc = 0.0;
-  for (int b = threadIdx.x; b < nblk; b += 256) acc += partial[(size_t)j * nblk + b];
-  double s = block_sum(acc, red);
-  if (threadIdx.x == 0) {
-    if (take_sqrt) s = sqrt(s);
-    if (h) h[j] = s;
-    if (hacc) hacc[j] += s;
-  }
+  for (size_t e = (size_t)blockIdx.x * 256 + threadIdx.x; e < len; e += stride) acc += w[e] * w[e];
+  const double s = block_sum(acc, red);
+  if (threadIdx.x == 0) partial[blockIdx.x] = s;
 }
 
-hipError_t launch_dots_final_sqrt(int nblk, const double* partial, double* h, hipStream_t st) {
-  k_dots_final<<<1, 256, 0, st>>>(nblk, partial, h, nullptr, 1);
+// out = sqrt(sum of partial), fixed order
+__global__ __launch_bounds__(256) void k_norm_final(int nblk, const double* partial, double* out) {
+  __shared__ double red[4];
+  double acc = 0.0;
+  for (int b = threadIdx.x; b < nblk; b += 256) acc += partial[b];
+  const double s = block_sum(acc, red);
+  if (threadIdx.x == 0) out[0] = sqrt(s);
+}
+
+// out = ||w|| of a short vector, one workgroup in place of the two launches above.
+__global__ __launch_bounds__(1024) void k_norm_small(int len, const double* __restrict__ w, double* out) {
+  __shared__ double red[16];
+  double acc = 0.0;
+  for (int e = threadIdx.x; e < len; e += 1024) acc += w[e] * w[e];
+  const double s = block_sum(acc, red);
+  if (threadIdx.x == 0) out[0] = sqrt(s);
+}
+
+// out = ||w||; partial: scratch of nblk sums.  One workgroup up to 16384 values: 6 us there, as
+// long as the two launches.
+hipError_t launch_norm(size_t len, const double* w, double* partial, int nblk, double* out, hipStream_t st) {
+  if (len <= 16384) {
+    k_norm_small<<<1, 1024, 0, st>>>((int)len, w, out);
+    return hipGetLastError();
+  }
+  k_norm_parts<<<nblk, 256, 0, st>>>(len, w, partial, nblk);
+  k_norm_final<<<1, 256, 0, st>>>(nblk, partial, out);
   return hipGetLastError();
 }
 
@@ -219,6 +219,77 @@ __global__ __launch_bounds__(256) void k_arnoldi_normalize(size_t len, const dou
   }
 }
 
+// The same step for short vectors, one workgroup, w in LDS: the four launches of a vector of 864
+// take 21 us and the gaps between them, whatever its length, and the sums themselves 2.
+// A wave takes every 16th dot product over the whole length.
+__global__ __launch_bounds__(1024) void k_arnoldi_small(int k, int len, double* __restrict__ V, size_t ldv, int ldh,
+                                                        double* __restrict__ H, double* __restrict__ cs,
+                                                        double* __restrict__ sn, double* __restrict__ g,
+                                                        double* __restrict__ resid) {
+  extern __shared__ double sm[];
+  const int kk = k + 1, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  double *ws = sm, *h = ws + len, *h2 = h + kk + 1, *c = h2 + kk, *s = c + kk, *red = s + kk;
+  double* w = V + (size_t)kk * ldv;
+  for (int e = tid; e < len; e += 1024) ws[e] = w[e];
+  for (int j = tid; j < k; j += 1024) {
+    c[j] = cs[j];
+    s[j] = sn[j];
+  }
+  const double gk = g[k];
+  __syncthreads();
+  double nsq = 0.0;
+  for (int pass = 0; pass < 2; ++pass) {
+    double* hp = pass ? h2 : h;
+    for (int j = wv; j < kk; j += 16) {
+      const double* v = V + (size_t)j * ldv;
+      double acc = 0.0;
+#pragma unroll 4
+      for (int e = lane; e < len; e += 64) acc += v[e] * ws[e];
+      acc = wave_sum(acc);
+      if (lane == 0) hp[j] = acc;
+    }
+    __syncthreads();
+    for (int e = tid; e < len; e += 1024) {
+      double acc = 0.0;
+#pragma unroll 4
+      for (int j = 0; j < kk; ++j) acc += V[(size_t)j * ldv + e] * hp[j];
+      const double v = ws[e] - acc;
+      ws[e] = v;
+      nsq += v * v;
+    }
+    if (pass == 0) {
+      nsq = 0.0;
+      __syncthreads();
+    }
+  }
+  nsq = wave_sum(nsq);
+  if (lane == 0) red[wv] = nsq;
+  __syncthreads();
+  double sum = 0.0;
+  for (int i = 0; i < 16; ++i) sum += red[i];
+  const double nv = sqrt(sum), f = nv != 0.0 ? 1.0 / nv : 0.0;
+  for (int e = tid; e < len; e += 1024) w[e] = ws[e] * f;
+  if (tid == 0) {
+    // column k of H with the earlier rotations, and a new one
+    double a = h[0] + h2[0];
+    double* col = H + (size_t)k * ldh;
+    for (int j = 0; j < k; ++j) {
+      const double b = h[j + 1] + h2[j + 1];
+      col[j] = c[j] * a + s[j] * b;
+      a = -s[j] * a + c[j] * b;
+    }
+    const double den = hypot(a, nv);
+    const double cn = den > 0.0 ? a / den : 1.0, sv = den > 0.0 ? nv / den : 0.0;
+    cs[k] = cn;
+    sn[k] = sv;
+    col[k] = den;
+    col[k + 1] = 0.0;
+    g[k + 1] = -sv * gk;
+    g[k] = cn * gk;
+    resid[0] = fabs(sv * gk);
+  }
+}
+
 hipError_t launch_arnoldi(int k, size_t len, double* V, size_t ldv, double* partial, size_t pstride,
                           int nblk, int ldh, double* H, double* cs, double* sn, double* g,
                           double* resid, hipStream_t st) {
@@ -227,6 +298,14 @@ hipError_t launch_arnoldi(int k, size_t len, double* V, size_t ldv, double* part
   double* hcol = H + (size_t)k * ldh;
   double *P1 = partial, *P2 = partial + pstride, *P3 = partial + 2 * pstride;
   const size_t hs = (size_t)kk * sizeof(double);
+  // One workgroup where its passes over V (8 len kk bytes each, from one CU) take less than the
+  // launches.  Whole float64 solves with four launches and with one, in us: len 864 866 -> 692, 1584 979
+  // -> 832, 3168 1047 -> 950, 4680 1320 -> 1259, 6336 (18 iterations) 1540 -> 1557, 9360 1725 -> 1906.
+  if (len <= 5120 && len * kk <= 81920) {
+    const size_t lds = (len + 4 * (size_t)kk + 1 + 16) * sizeof(double);
+    k_arnoldi_small<<<1, 1024, lds, st>>>(k, (int)len, V, ldv, ldh, H, cs, sn, g, resid);
+    return hipGetLastError();
+  }
   k_arnoldi_dots<<<nblk, 256, 0, st>>>(kk, len, V, ldv, w, P1, nblk);
   k_arnoldi_update_dots<<<nblk, 256, hs, st>>>(kk, len, V, ldv, P1, P2, nblk, hcol, w);
   k_arnoldi_update_norm<<<nblk, 256, hs, st>>>(kk, len, V, ldv, P2, P3, nblk, hcol, w);

@@ -120,8 +120,7 @@ hipError_t launch_combine(int N, int M, int nsplit, const double* part, double c
                           double cb, double* out, hipStream_t st);
 
 // ---- Krylov (k_krylov.hip) --------------------------------------------------------
-hipError_t launch_dots(int kk, size_t len, const double* V, size_t ldv, const double* w,
-                       double* partial, int nblk, hipStream_t st);
+hipError_t launch_norm(size_t len, const double* w, double* partial, int nblk, double* out, hipStream_t st);
 // w -= sum_j V[j] h[j]  (or w = sum_j V[j] h[j] if overwrite)
 hipError_t launch_vupdate(int kk, size_t len, const double* V, size_t ldv, const double* h,
                           double* w, int overwrite, hipStream_t st);
@@ -129,7 +128,6 @@ hipError_t launch_axpby(size_t len, double a, const double* x, double b, const d
                         double* out, hipStream_t st);
 hipError_t launch_backsolve(int m, int ldh, const double* H, const double* g, double* y,
                             hipStream_t st);
-hipError_t launch_dots_final_sqrt(int nblk, const double* partial, double* h, hipStream_t st);
 // GMRES cycle start: V0 = r / rnorm (0 if rnorm = 0), g[0] = rnorm and g[1..ng) = 0,
 // H[0..nh) = 0.
 hipError_t launch_gmres_init(size_t len, const double* r, double rnorm, double* V0, int ng, double* g,

@@ -904,8 +904,7 @@ static rbm_status wait_pinned(rbm_ctx* c, volatile double* p, double* out) {
 static rbm_status norm_to_pinned(rbm_ctx* c, const double* w, int slot, size_t len = 0) {
   if (len == 0) len = 3 * (size_t)c->n * c->M;
   c->pinned[slot] = -1.0;
-  HIPCHECK(launch_dots(1, len, w, len, w, c->partial, c->nblk, c->st));
-  HIPCHECK(launch_dots_final_sqrt(c->nblk, c->partial, c->pinned_dev + slot, c->st));
+  HIPCHECK(launch_norm(len, w, c->partial, c->nblk, c->pinned_dev + slot, c->st));
   return RBM_OK;
 }
 
