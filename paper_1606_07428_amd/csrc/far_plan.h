@@ -64,6 +64,15 @@ inline FarChunks far_chunks(int N, int nsplit) {
   return {s1, (int)c1, (int)c2};
 }
 
+// Whether the workgroups of an ordered sum pack their own sources (a thread each) instead of a
+// launch before it: every target block packs them again, which costs less than the launch while
+// a chunk is one load per thread.  Float64 solves with the launch and without, us: 288 points 670
+// -> 632, 1560 1270 -> 1203, 3120 1717 -> 1641, 4992 2353 -> 2306, 8112 3569 -> 3493.
+inline bool far_packs(int N, int nsplit) {
+  const FarChunks fc = far_chunks(N, nsplit);
+  return N <= 8192 && fc.c1 <= 256 && fc.c2 <= 256;
+}
+
 // ---- sums with every unordered pair of points evaluated once (k_far_sym.hip) -----------
 // nb blocks of tb points; block row i pairs with the h next blocks (cyclic), rows of the nb in
 // phases of `rows`.  In a phase that starts at row0 the blocks row0 .. row0 + nj - 1 (cyclic) are

@@ -175,11 +175,8 @@ template hipError_t launch_far<float>(int, int, int, const float*, const float*,
 // q_g = W_g * z_g (z rotated to the lab frame first when given in body frames); with nor the
 // normals Nn are packed too.
 template <typename T>
-__global__ void k_pack(int N, int M, const double* __restrict__ X, const double* __restrict__ W,
-                       const double* __restrict__ Rm, const double* __restrict__ z, int z_is_body,
-                       const double* __restrict__ Nn, Src8<T>* __restrict__ src, Nor4<T>* __restrict__ nor) {
-  const int g = blockIdx.x * blockDim.x + threadIdx.x;
-  if (g >= N) return;
+__device__ __forceinline__ Src8<T> pack_source(int g, int N, int M, const double* X, const double* W, const double* Rm,
+                                               const double* z, int z_is_body) {
   double v0 = z[g], v1 = z[N + g], v2 = z[2 * (size_t)N + g];
   if (z_is_body) {
     const double* R = Rm + 9 * (g / M);
@@ -198,7 +195,16 @@ __global__ void k_pack(int N, int M, const double* __restrict__ X, const double*
   s.v[5] = (T)(w * v2);
   s.v[6] = 0;
   s.v[7] = 0;
-  src[g] = s;
+  return s;
+}
+
+template <typename T>
+__global__ void k_pack(int N, int M, const double* __restrict__ X, const double* __restrict__ W,
+                       const double* __restrict__ Rm, const double* __restrict__ z, int z_is_body,
+                       const double* __restrict__ Nn, Src8<T>* __restrict__ src, Nor4<T>* __restrict__ nor) {
+  const int g = blockIdx.x * blockDim.x + threadIdx.x;
+  if (g >= N) return;
+  src[g] = pack_source<T>(g, N, M, X, W, Rm, z, z_is_body);
   if (nor) {
     Nor4<T> m;
     m.v[0] = (T)Nn[g];
@@ -224,6 +230,64 @@ template hipError_t launch_pack_sources<double>(int, int, const double*, const d
 template hipError_t launch_pack_sources<float>(int, int, const double*, const double*,
                                                 const double*, const double*, int, const double*, void*,
                                                 void*, hipStream_t);
+
+// The ordered traction sum of few points without the packing launch: every workgroup packs
+// its own chunk of sources into LDS (a thread each) and its lanes read them from there.  Same
+// operations in the same order as k_pack and k_far.  Bound by latency: a launch, the loads, the
+// chunk's serial sum (5.4 us at 288 points, as k_far alone).
+template <typename T>
+__global__ __launch_bounds__(256) void k_far_packing(int N, int M, const T* __restrict__ tx, const T* __restrict__ tn,
+                                                     const double* __restrict__ X, const double* __restrict__ W,
+                                                     const double* __restrict__ Rm, const double* __restrict__ z,
+                                                     int z_is_body, double* __restrict__ part, int s1, int c1, int c2) {
+  __shared__ Src8<T> ls[256];
+  const int split = blockIdx.y, tid = threadIdx.x;
+  const int b0 = split < s1 ? split * c1 : s1 * c1 + (split - s1) * c2;
+  const int b1 = min(N, b0 + (split < s1 ? c1 : c2));
+  if (b0 + tid < b1) ls[tid] = pack_source<T>(b0 + tid, N, M, X, W, Rm, z, z_is_body);
+  const int base = blockIdx.x * 256, a = min(base + tid, N - 1);
+  const T xa = tx[a], ya = tx[N + a], za = tx[2 * N + a], nx = tn[a], ny = tn[N + a], nz = tn[2 * N + a];
+  T ax = 0, ay = 0, az = 0;
+  const int blo_t = (a / M) * M;
+  const int last = min(N, base + 256) - 1, blo = (base / M) * M, bhi = (last / M + 1) * M;
+  __syncthreads();
+  if (b1 <= blo || b0 >= bhi) {
+#pragma unroll 4
+    for (int b = b0; b < b1; ++b) Pair<T, 0>::add(xa, ya, za, nx, ny, nz, ls[b - b0], ax, ay, az);
+  } else {
+    for (int b = b0; b < b1; ++b) {
+      T px = 0, py = 0, pz = 0;
+      Pair<T, 0>::add(xa, ya, za, nx, ny, nz, ls[b - b0], px, py, pz);
+      const bool other = (unsigned)(b - blo_t) >= (unsigned)M;
+      ax += other ? px : (T)0;
+      ay += other ? py : (T)0;
+      az += other ? pz : (T)0;
+    }
+  }
+  if (base + tid < N) {
+    const double scale = kind_scale(0) * Pair<T, 0>::kPost;
+    double* o = part + (size_t)split * 3 * N;
+    o[a] = scale * (double)ax;
+    o[N + a] = scale * (double)ay;
+    o[2 * (size_t)N + a] = scale * (double)az;
+  }
+}
+
+template <typename T>
+hipError_t launch_far_packing(int N, int M, const T* tx, const T* tn, const double* X, const double* W,
+                              const double* Rm, const double* z, int z_is_body, double* part, int nsplit,
+                              hipStream_t st) {
+  if (N < 1 || nsplit < 1 || !far_packs(N, nsplit)) return hipErrorInvalidValue;
+  const FarChunks fc = far_chunks(N, nsplit);
+  k_far_packing<T><<<dim3((N + 255) / 256, nsplit), 256, 0, st>>>(N, M, tx, tn, X, W, Rm, z, z_is_body, part, fc.s1,
+                                                                  fc.c1, fc.c2);
+  return hipGetLastError();
+}
+
+template hipError_t launch_far_packing<double>(int, int, const double*, const double*, const double*, const double*,
+                                         const double*, const double*, int, double*, int, hipStream_t);
+template hipError_t launch_far_packing<float>(int, int, const float*, const float*, const double*, const double*,
+                                        const double*, const double*, int, double*, int, hipStream_t);
 
 // out = ca*a + cb*(R_i b_body) + cp*sum_s part[s]   (fixed summation order); out may be
 // a, not b_body.  The slot sum over the split is the memory-bound part.

@@ -802,19 +802,26 @@ static rbm_status far_traction(rbm_ctx* c, SolveState& S, const double* x, int x
     S.fmm_applies++;
     return near_correction(c, S, 0, x, x_is_body, 1);
   }
-  if (prec == 0) {
-    HIPCHECK(launch_pack_sources<double>(N, c->M, c->X, c->W, c->Rm, x, x_is_body, c->Nn, c->src, c->nor, c->st));
+  // the packed sources serve the near correction too
+  const auto sum = [&](auto one, const auto* tx, const auto* tn, auto& events) -> rbm_status {
+    using T = decltype(one);
+    const int split = split_for(c, N);
+    const bool packs = !c->pu && far_packs(N, split);
+    if (!packs)
+      HIPCHECK(launch_pack_sources<T>(N, c->M, c->X, c->W, c->Rm, x, x_is_body, c->Nn, c->src, c->nor, c->st));
     Timer t(c);
-    HIPCHECK(far_sum<double>(c, 0, N, c->M, c->X, c->Nn, &c->far_base));
+    if (packs) {
+      HIPCHECK(launch_far_packing<T>(N, c->M, tx, tn, c->X, c->W, c->Rm, x, x_is_body, c->part, split, c->st));
+      c->far_base = split;
+    } else {
+      HIPCHECK(far_sum<T>(c, 0, N, c->M, tx, tn, &c->far_base));
+    }
     t.stop();
-    if (t.on) S.trac_ev.push_back({c->ev_used - 2, c->ev_used - 1});
-  } else {
-    HIPCHECK(launch_pack_sources<float>(N, c->M, c->X, c->W, c->Rm, x, x_is_body, c->Nn, c->src, c->nor, c->st));
-    Timer t(c);
-    HIPCHECK(far_sum<float>(c, 0, N, c->M, c->Xf, c->Nf, &c->far_base));
-    t.stop();
-    if (t.on) S.trac32_ev.push_back({c->ev_used - 2, c->ev_used - 1});
-  }
+    if (t.on) events.push_back({c->ev_used - 2, c->ev_used - 1});
+    return RBM_OK;
+  };
+  rbm_status s = prec == 0 ? sum(double(), c->X, c->Nn, S.trac_ev) : sum(float(), c->Xf, c->Nf, S.trac32_ev);
+  if (s != RBM_OK) return s;
   c->far_nslots = c->far_base + (c->pu ? 1 : 0);
   S.far_pairs += (double)N * N - (double)c->n * c->M * c->M;
   return near_correction(c, S, 0, x, x_is_body, prec == 0 ? 0 : 1);
