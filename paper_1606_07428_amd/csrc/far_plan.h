@@ -64,13 +64,18 @@ inline FarChunks far_chunks(int N, int nsplit) {
   return {s1, (int)c1, (int)c2};
 }
 
-// Whether the workgroups of an ordered sum pack their own sources (a thread each) instead of a
-// launch before it: every target block packs them again, which costs less than the launch while
-// a chunk is one load per thread.  Float64 solves with the launch and without, us: 288 points 670
-// -> 632, 1560 1270 -> 1203, 3120 1717 -> 1641, 4992 2353 -> 2306, 8112 3569 -> 3493.
-inline bool far_packs(int N, int nsplit) {
-  const FarChunks fc = far_chunks(N, nsplit);
-  return N <= 8192 && fc.c1 <= 256 && fc.c2 <= 256;
+// Ordered sums of few points in one launch (k_far_packing): 64 targets per workgroup, a quarter of its
+// chunk of sources per wave; chunks (partial-sum slots) for one round of the 2048 resident workgroups,
+// of at least 8 sources a wave and at most 256 (a thread packs one, 16 KiB of LDS); 0: not
+// taken.  Whole rbm_far_traction_static, us, with the launches apart (up to 96 chunks for 256
+// targets) and with this: float64 300 points 14.7 -> 12.4, 1000 18.4 -> 12.5, 5003 46.0 -> 34.6, 8000
+// 80.0 -> 69.5, 10,000 110 -> 102, 12,000 143 -> 148; float32 5003 40 -> 27, 10,000 72 -> 62, 12,000
+// 91 -> 84, 16,000 130 -> 136.
+constexpr int kPackingMax = 10240;
+inline int far_packing_slots(int N) {
+  if (N < 1 || N > kPackingMax) return 0;
+  const int blocks = (N + 63) / 64, fill = std::min(kResident / blocks, (N + 4 * kMinSources - 1) / (4 * kMinSources));
+  return std::max({1, (N + 255) / 256, fill});
 }
 
 // ---- sums with every unordered pair of points evaluated once (k_far_sym.hip) -----------

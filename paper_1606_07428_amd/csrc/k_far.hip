@@ -231,63 +231,78 @@ template hipError_t launch_pack_sources<float>(int, int, const double*, const do
                                                 const double*, const double*, int, const double*, void*,
                                                 void*, hipStream_t);
 
-// The ordered traction sum of few points without the packing launch: every workgroup packs
-// its own chunk of sources into LDS (a thread each) and its lanes read them from there.  Same
-// operations in the same order as k_pack and k_far.  Bound by latency: a launch, the loads, the
-// chunk's serial sum (5.4 us at 288 points, as k_far alone).
-template <typename T>
-__global__ __launch_bounds__(256) void k_far_packing(int N, int M, const T* __restrict__ tx, const T* __restrict__ tn,
-                                                     const double* __restrict__ X, const double* __restrict__ W,
+// The ordered sum of few points without the launches before it: a workgroup takes 64 targets, packs
+// its chunk of sources into LDS (a thread each) and gives each wave a quarter of them; the waves'
+// sums are added through LDS.  Same operations as the casts, k_pack and k_far.
+// Bound by latency: a launch, the loads, a wave's serial sum; a quarter of the partial sums that one
+// chunk per workgroup of 256 targets writes (5003 points: far_traction_static 43 -> 34 us).
+template <typename T, int KIND>
+__global__ __launch_bounds__(256) void k_far_packing(int N, int M, int chunk, const double* __restrict__ X,
+                                                     const double* __restrict__ Nn, const double* __restrict__ W,
                                                      const double* __restrict__ Rm, const double* __restrict__ z,
-                                                     int z_is_body, double* __restrict__ part, int s1, int c1, int c2) {
+                                                     int z_is_body, double* __restrict__ part) {
   __shared__ Src8<T> ls[256];
-  const int split = blockIdx.y, tid = threadIdx.x;
-  const int b0 = split < s1 ? split * c1 : s1 * c1 + (split - s1) * c2;
-  const int b1 = min(N, b0 + (split < s1 ? c1 : c2));
-  if (b0 + tid < b1) ls[tid] = pack_source<T>(b0 + tid, N, M, X, W, Rm, z, z_is_body);
-  const int base = blockIdx.x * 256, a = min(base + tid, N - 1);
-  const T xa = tx[a], ya = tx[N + a], za = tx[2 * N + a], nx = tn[a], ny = tn[N + a], nz = tn[2 * N + a];
+  __shared__ T red[3][3][64];
+  const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int b0 = blockIdx.y * chunk, cnt = min(N - b0, chunk);
+  if (tid < cnt) ls[tid] = pack_source<T>(b0 + tid, N, M, X, W, Rm, z, z_is_body);
+  const int base = blockIdx.x * 64, a = min(base + lane, N - 1);
+  const T xa = (T)X[a], ya = (T)X[N + a], za = (T)X[2 * N + a];
+  T nx = 0, ny = 0, nz = 0;
+  if (KIND == 0) {
+    nx = (T)Nn[a];
+    ny = (T)Nn[N + a];
+    nz = (T)Nn[2 * N + a];
+  }
   T ax = 0, ay = 0, az = 0;
   const int blo_t = (a / M) * M;
-  const int last = min(N, base + 256) - 1, blo = (base / M) * M, bhi = (last / M + 1) * M;
+  const int last = min(N, base + 64) - 1, blo = (base / M) * M, bhi = (last / M + 1) * M;
+  const int each = (chunk + 3) / 4, k0 = wv * each, k1 = min(cnt, k0 + each);
   __syncthreads();
-  if (b1 <= blo || b0 >= bhi) {
+  if (b0 + k1 <= blo || b0 + k0 >= bhi) {
 #pragma unroll 4
-    for (int b = b0; b < b1; ++b) Pair<T, 0>::add(xa, ya, za, nx, ny, nz, ls[b - b0], ax, ay, az);
+    for (int k = k0; k < k1; ++k) Pair<T, KIND>::add(xa, ya, za, nx, ny, nz, ls[k], ax, ay, az);
   } else {
-    for (int b = b0; b < b1; ++b) {
+    for (int k = k0; k < k1; ++k) {
       T px = 0, py = 0, pz = 0;
-      Pair<T, 0>::add(xa, ya, za, nx, ny, nz, ls[b - b0], px, py, pz);
-      const bool other = (unsigned)(b - blo_t) >= (unsigned)M;
+      Pair<T, KIND>::add(xa, ya, za, nx, ny, nz, ls[k], px, py, pz);
+      const bool other = (unsigned)(b0 + k - blo_t) >= (unsigned)M;
       ax += other ? px : (T)0;
       ay += other ? py : (T)0;
       az += other ? pz : (T)0;
     }
   }
-  if (base + tid < N) {
-    const double scale = kind_scale(0) * Pair<T, 0>::kPost;
-    double* o = part + (size_t)split * 3 * N;
-    o[a] = scale * (double)ax;
-    o[N + a] = scale * (double)ay;
-    o[2 * (size_t)N + a] = scale * (double)az;
+  if (wv > 0) {
+    red[wv - 1][0][lane] = ax;
+    red[wv - 1][1][lane] = ay;
+    red[wv - 1][2][lane] = az;
+  }
+  __syncthreads();
+  if (wv == 0 && base + lane < N) {
+    const double scale = kind_scale(KIND) * Pair<T, KIND>::kPost;
+    double* o = part + (size_t)blockIdx.y * 3 * N;
+    auto sum = [&](T v, int c) {
+      return scale * (((double)v + (double)red[0][c][lane]) + ((double)red[1][c][lane] + (double)red[2][c][lane]));
+    };
+    o[a] = sum(ax, 0);
+    o[N + a] = sum(ay, 1);
+    o[2 * (size_t)N + a] = sum(az, 2);
   }
 }
 
-template <typename T>
-hipError_t launch_far_packing(int N, int M, const T* tx, const T* tn, const double* X, const double* W,
-                              const double* Rm, const double* z, int z_is_body, double* part, int nsplit,
-                              hipStream_t st) {
-  if (N < 1 || nsplit < 1 || !far_packs(N, nsplit)) return hipErrorInvalidValue;
-  const FarChunks fc = far_chunks(N, nsplit);
-  k_far_packing<T><<<dim3((N + 255) / 256, nsplit), 256, 0, st>>>(N, M, tx, tn, X, W, Rm, z, z_is_body, part, fc.s1,
-                                                                  fc.c1, fc.c2);
-  return hipGetLastError();
+hipError_t launch_far_packing(int kind, int prec, int N, int M, const double* X, const double* Nn, const double* W,
+                              const double* Rm, const double* z, int z_is_body, double* part, hipStream_t st) {
+  const int slots = far_packing_slots(N);
+  if (slots < 1 || M < 1 || kind < 0 || kind > 1) return hipErrorInvalidValue;
+  const int chunk = (N + slots - 1) / slots;
+  const dim3 grid((N + 63) / 64, slots);
+  auto run = [&](auto kern) {
+    kern<<<grid, 256, 0, st>>>(N, M, chunk, X, Nn, W, Rm, z, z_is_body, part);
+    return hipGetLastError();
+  };
+  if (prec == 0) return kind == 0 ? run(k_far_packing<double, 0>) : run(k_far_packing<double, 1>);
+  return kind == 0 ? run(k_far_packing<float, 0>) : run(k_far_packing<float, 1>);
 }
-
-template hipError_t launch_far_packing<double>(int, int, const double*, const double*, const double*, const double*,
-                                         const double*, const double*, int, double*, int, hipStream_t);
-template hipError_t launch_far_packing<float>(int, int, const float*, const float*, const double*, const double*,
-                                        const double*, const double*, int, double*, int, hipStream_t);
 
 // out = ca*a + cb*(R_i b_body) + cp*sum_s part[s]   (fixed summation order); out may be
 // a, not b_body.  The slot sum over the split is the memory-bound part.

@@ -805,14 +805,14 @@ static rbm_status far_traction(rbm_ctx* c, SolveState& S, const double* x, int x
   // the packed sources serve the near correction too
   const auto sum = [&](auto one, const auto* tx, const auto* tn, auto& events) -> rbm_status {
     using T = decltype(one);
-    const int split = split_for(c, N);
-    const bool packs = !c->pu && far_packs(N, split);
-    if (!packs)
+    const int slots = c->pu ? 0 : far_packing_slots(N);
+    if (slots == 0)
       HIPCHECK(launch_pack_sources<T>(N, c->M, c->X, c->W, c->Rm, x, x_is_body, c->Nn, c->src, c->nor, c->st));
     Timer t(c);
-    if (packs) {
-      HIPCHECK(launch_far_packing<T>(N, c->M, tx, tn, c->X, c->W, c->Rm, x, x_is_body, c->part, split, c->st));
-      c->far_base = split;
+    if (slots > 0) {
+      HIPCHECK(launch_far_packing(0, sizeof(T) == 8 ? 0 : 1, N, c->M, c->X, c->Nn, c->W, c->Rm, x, x_is_body, c->part,
+                                  c->st));
+      c->far_base = slots;
     } else {
       HIPCHECK(far_sum<T>(c, 0, N, c->M, tx, tn, &c->far_base));
     }
@@ -1713,7 +1713,9 @@ extern "C" rbm_status rbm_far_traction(rbm_ctx* c, int n_points, int M, const do
   int nsplit = 0;
   hipStream_t st = c->st;
   const size_t N3 = 3 * (size_t)n_points;
-  if (precision == 0) {
+  if ((nsplit = far_packing_slots(n_points)) > 0) {
+    HIPCHECK(launch_far_packing(0, precision, n_points, M, X, Nrm, nullptr, nullptr, q, 0, c->part, st));
+  } else if (precision == 0) {
     HIPCHECK(launch_pack_sources<double>(n_points, M, X, nullptr, nullptr, q, 0, Nrm, c->src, c->nor, st));
     HIPCHECK(far_sum<double>(c, 0, n_points, M, X, Nrm, &nsplit));
   } else {
@@ -1762,7 +1764,9 @@ extern "C" rbm_status rbm_far_stokeslet(rbm_ctx* c, int n_points, int M, const d
   int nsplit = 0;
   hipStream_t st = c->st;
   const size_t N3 = 3 * (size_t)n_points;
-  if (precision == 0) {
+  if ((nsplit = far_packing_slots(n_points)) > 0) {
+    HIPCHECK(launch_far_packing(1, precision, n_points, M, X, nullptr, nullptr, nullptr, q, 0, c->part, st));
+  } else if (precision == 0) {
     HIPCHECK(launch_pack_sources<double>(n_points, M, X, nullptr, nullptr, q, 0, nullptr, c->src, nullptr, st));
     HIPCHECK(far_sum<double>(c, 1, n_points, M, X, nullptr, &nsplit));
   } else {

@@ -104,7 +104,11 @@ extern "C" rbm_status rbm_far_traction_static(int n_points, int M, const double*
   while (split > 1 && scratch_bytes(N, split, precision) > kOrderedBytes) --split;
   void* src = base;
   double* part = reinterpret_cast<double*>(base + align256(N * (precision == 0 ? 64 : 32)));
-  if (precision == 0) {
+  if (far_packing_slots(n_points) > 0) {
+    split = far_packing_slots(n_points);
+    if ((e = launch_far_packing(0, precision, n_points, M, X, Nrm, nullptr, nullptr, q, 0, part, st)) != hipSuccess)
+      return set_last_error(RBM_E_DEVICE, hipGetErrorString(e));
+  } else if (precision == 0) {
     if ((e = launch_pack_sources<double>(n_points, M, X, nullptr, nullptr, q, 0, nullptr, src, nullptr, st)) != hipSuccess ||
         (e = launch_far<double>(0, n_points, M, X, Nrm, src, part, split, st)) != hipSuccess)
       return set_last_error(RBM_E_DEVICE, hipGetErrorString(e));
