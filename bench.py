@@ -46,16 +46,18 @@ FP64_PEAK_TFLOPS = 78.6      # MI355X vector FP64
 FP32_PEAK_TFLOPS = 157.3     # MI355X vector FP32
 TRACTION_FLOPS_PER_PAIR = 30
 STOKESLET_FLOPS_PER_PAIR = 28
-# far-sum kernels of a solve: name, info fields (summed ms, launches), flops per pair, peak,
-# the sources their traffic record is tied to
+# far sums of a solve: name, info fields (summed ms, launches), flops per pair, peak, the sources
+# their traffic record is tied to.  Above the sizes that far_plan.h states (56,000 points for the
+# fused sum, 15,000 and 36,000 for the float64 and float32 traction) k_far_sym evaluates them,
+# every unordered pair once; pairs and flops are counted per direction all the same.
 FAR_KERNELS = [
     ("k_far_ts (float64 traction + Stokeslet)", "ms_fused", "n_fused",
      TRACTION_FLOPS_PER_PAIR + STOKESLET_FLOPS_PER_PAIR, FP64_PEAK_TFLOPS,
-     ("k_far_fused.hip", "pair.h", "far_plan.h")),
+     ("k_far_fused.hip", "k_far_sym.hip", "pair.h", "far_plan.h")),
     ("k_far<double, traction>", "ms_traction", "n_traction", TRACTION_FLOPS_PER_PAIR, FP64_PEAK_TFLOPS,
-     ("k_far.hip", "pair.h", "far_plan.h")),
+     ("k_far.hip", "k_far_sym.hip", "pair.h", "far_plan.h")),
     ("k_far<float, traction>", "ms_traction32", "n_traction32", TRACTION_FLOPS_PER_PAIR, FP32_PEAK_TFLOPS,
-     ("k_far.hip", "pair.h", "far_plan.h")),
+     ("k_far.hip", "k_far_sym.hip", "pair.h", "far_plan.h")),
 ]
 
 # Per workload: near-singular upsampling order (0 = plain smooth rule), fast multipole order
@@ -121,7 +123,7 @@ def _cpu_baseline(w, budget_s, threads):
                       f"sources ({pairs:.3e} pairs, {dt:.1f} s, NumPy in {threads} threads)"}
 
 
-def _kernel_source_hash(files=("k_far.hip", "pair.h", "far_plan.h")):
+def _kernel_source_hash(files=("k_far.hip", "k_far_sym.hip", "pair.h", "far_plan.h")):
     """sha256 of a far-sum kernel's sources (the kernel file, its pair arithmetic and its
     source-chunk plan)."""
     import hashlib

@@ -244,15 +244,14 @@ __host__ __device__ inline int singular_work(int p) {
   return w > ce ? w : ce;
 }
 
-// One workgroup per (target, shape).  The products' sums and differences over +-n of 8 colatitudes at a time
-// go through LDS (one e of the four rows a lane holds), so that two workgroups fit a CU.  NIT: passes of 256 threads over the (l, m) x 3 sums of step
-// 3; MT: 16-wide tiles of m.
+// One workgroup per (target, shape).  The sums and differences over +-n of 8 colatitudes at a time go
+// through LDS (one e of the four rows a lane holds), so that two workgroups fit a CU.  NIT: passes
+// of 256 threads over the (l, m) x 3 sums of step 3; MT: 16-wide tiles of m.
 template <int NIT, int MT>
-__global__ __launch_bounds__(256, NIT == 2 ? 2 : 1) void k_singular(SingularTables T, double eta, const double* __restrict__ coef_all,
-                                                     const double* __restrict__ gx_all,
-                                                     const double* __restrict__ gn_all,
-                                                     const double* __restrict__ rW, const double* __restrict__ tab,
-                                                     double* __restrict__ Sop, double* __restrict__ Kop) {
+__global__ __launch_bounds__(256, NIT == 2 ? 2 : 1) void k_singular(
+    SingularTables T, double eta, const double* __restrict__ coef_all, const double* __restrict__ gx_all,
+    const double* __restrict__ gn_all, const double* __restrict__ rW, const double* __restrict__ tab,
+    double* __restrict__ Sop, double* __restrict__ Kop) {
   extern __shared__ double lds[];
   const int p = T.p, ps = T.ps, NIP = T.NIP, nc = (p + 1) * (p + 1), M = (p + 1) * 2 * p, M3 = 3 * M;
   const int MQ = (p + 1 + 3) / 4 * 4, p1 = p + 1;
