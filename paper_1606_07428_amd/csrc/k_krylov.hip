@@ -221,8 +221,10 @@ __global__ __launch_bounds__(256) void k_arnoldi_normalize(size_t len, const dou
 
 // The same step for short vectors, one workgroup, w in LDS: the four launches of a vector of 864
 // take 21 us and the gaps between them, whatever its length, and the sums themselves 2.
-// A wave takes every 16th dot product over the whole length.
-__global__ __launch_bounds__(1024) void k_arnoldi_small(int k, int len, double* __restrict__ V, size_t ldv, int ldh,
+// A wave takes every 16th dot product over the whole length.  With part, w is formed here: V[k] plus
+// the sums of part [nslots][len], in the order of k_combine.
+__global__ __launch_bounds__(1024) void k_arnoldi_small(int k, int len, double* __restrict__ V, size_t ldv,
+                                                        const double* __restrict__ part, int nslots, int ldh,
                                                         double* __restrict__ H, double* __restrict__ cs,
                                                         double* __restrict__ sn, double* __restrict__ g,
                                                         double* __restrict__ resid) {
@@ -230,7 +232,23 @@ __global__ __launch_bounds__(1024) void k_arnoldi_small(int k, int len, double* 
   const int kk = k + 1, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   double *ws = sm, *h = ws + len, *h2 = h + kk + 1, *c = h2 + kk, *s = c + kk, *red = s + kk;
   double* w = V + (size_t)kk * ldv;
-  for (int e = tid; e < len; e += 1024) ws[e] = w[e];
+  for (int e = tid; e < len; e += 1024) {
+    double v;
+    if (part) {
+      double q[4] = {0.0, 0.0, 0.0, 0.0};
+      int i = 0;
+      for (; i + 4 <= nslots; i += 4)
+#pragma unroll
+        for (int u = 0; u < 4; ++u) q[u] += part[(size_t)(i + u) * len + e];
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        if (i + u < nslots) q[u] += part[(size_t)(i + u) * len + e];
+      v = (q[0] + q[1]) + (q[2] + q[3]) + V[(size_t)k * ldv + e];
+    } else {
+      v = w[e];
+    }
+    ws[e] = v;
+  }
   for (int j = tid; j < k; j += 1024) {
     c[j] = cs[j];
     s[j] = sn[j];
@@ -290,9 +308,9 @@ __global__ __launch_bounds__(1024) void k_arnoldi_small(int k, int len, double* 
   }
 }
 
-hipError_t launch_arnoldi(int k, size_t len, double* V, size_t ldv, double* partial, size_t pstride,
-                          int nblk, int ldh, double* H, double* cs, double* sn, double* g,
-                          double* resid, hipStream_t st) {
+hipError_t launch_arnoldi(int k, size_t len, double* V, size_t ldv, const double* part, int nslots,
+                          double* partial, size_t pstride, int nblk, int ldh, double* H, double* cs, double* sn,
+                          double* g, double* resid, hipStream_t st) {
   const int kk = k + 1;
   double* w = V + (size_t)kk * ldv;
   double* hcol = H + (size_t)k * ldh;
@@ -301,9 +319,19 @@ hipError_t launch_arnoldi(int k, size_t len, double* V, size_t ldv, double* part
   // One workgroup where its passes over V (8 len kk bytes each, from one CU) take less than the
   // launches.  Whole float64 solves with four launches and with one, in us: len 864 866 -> 692, 1584 979
   // -> 832, 3168 1047 -> 950, 4680 1320 -> 1259, 6336 (18 iterations) 1540 -> 1557, 9360 1725 -> 1906.
-  if (len <= 5120 && len * kk <= 81920) {
+  const bool one = len <= 5120 && len * kk <= 81920;
+  // It also adds few partial sums faster than a launch of their own.  Solves with that launch and without, in
+  // us: 288 points (9 slots) 654 -> 626, 432 (14) 784 -> 773, 528 (17) 768 -> 763, 576 (18) 711 -> 712, 864 (27)
+  // 1045 -> 1120.
+  const bool add = one && part && nslots * len <= 24576;
+  if (part && !add) {
+    const hipError_t e = launch_combine((int)(len / 3), 1, nslots, part, 1.0, V + (size_t)k * ldv, 1.0, nullptr, nullptr,
+                                        0.0, w, st);
+    if (e != hipSuccess) return e;
+  }
+  if (one) {
     const size_t lds = (len + 4 * (size_t)kk + 1 + 16) * sizeof(double);
-    k_arnoldi_small<<<1, 1024, lds, st>>>(k, (int)len, V, ldv, ldh, H, cs, sn, g, resid);
+    k_arnoldi_small<<<1, 1024, lds, st>>>(k, (int)len, V, ldv, add ? part : nullptr, nslots, ldh, H, cs, sn, g, resid);
     return hipGetLastError();
   }
   k_arnoldi_dots<<<nblk, 256, 0, st>>>(kk, len, V, ldv, w, P1, nblk);

@@ -136,12 +136,13 @@ hipError_t launch_backsolve(int m, int ldh, const double* H, const double* g, do
 // H[0..nh) = 0.
 hipError_t launch_gmres_init(size_t len, const double* r, double rnorm, double* V0, int ng, double* g,
                              size_t nh, double* H, hipStream_t st);
-// One Arnoldi step after w = V[k+1] has been formed: CGS2 against V[0..k] (column k of H),
+// One Arnoldi step on w = V[k+1], formed before or (part) here as V[k] + sum of part's nslots slots of
+// len: CGS2 against V[0..k] (column k of H),
 // w normalised and ||w|| into H, the Givens rotations of column k, g updated and
 // |g_{k+1}| written to resid (which may be mapped host memory).  partial holds three
 // regions pstride doubles apart, each at least (k + 1) * nblk.
-hipError_t launch_arnoldi(int k, size_t len, double* V, size_t ldv, double* partial, size_t pstride,
-                          int nblk, int ldh, double* H, double* cs, double* sn, double* g,
+hipError_t launch_arnoldi(int k, size_t len, double* V, size_t ldv, const double* part, int nslots,
+                          double* partial, size_t pstride, int nblk, int ldh, double* H, double* cs, double* sn, double* g,
                           double* resid, hipStream_t st);
 
 // ---- learned warm start (k_mlp.hip) --------------------------------------------------

@@ -865,13 +865,12 @@ static rbm_status apply_A(rbm_ctx* c, SolveState& S, const double* x, double* ou
   return RBM_OK;
 }
 
-// out = v + K_far(w R P~^{-1} R^T v): the right-preconditioned operator A P^{-1}
-static rbm_status apply_AP(rbm_ctx* c, SolveState& S, int prec, const double* v, double* out) {
-  const int N = c->n * c->M;
+// The right-preconditioned operator A P^{-1} v = v + K_far(w R P~^{-1} R^T v): the partial sums of the
+// second term into c->part (c->far_nslots slots); launch_arnoldi adds v.
+static rbm_status apply_AP(rbm_ctx* c, SolveState& S, int prec, const double* v) {
   rbm_status s;
   if ((s = self_apply(c, S, 1, prec, v, c->yb)) != RBM_OK) return s;
   if ((s = far_traction(c, S, c->yb, 1, prec == 0 ? 0 : 1)) != RBM_OK) return s;
-  HIPCHECK(launch_combine(N, c->M, c->far_nslots, c->part, 1.0, v, 1.0, nullptr, nullptr, 0.0, out, c->st));
   S.matvecs++;
   return RBM_OK;
 }
@@ -945,10 +944,9 @@ static rbm_status gmres_cycle(rbm_ctx* c, SolveState& S, int prec, const double*
   // pinned host memory (two slots, alternating) and is read as soon as it does.
   const auto enqueue = [&](int j) -> rbm_status {
     rbm_status s2;
-    if ((s2 = apply_AP(c, S, prec, c->V + (size_t)j * len, c->V + (size_t)(j + 1) * len)) != RBM_OK)
-      return s2;
+    if ((s2 = apply_AP(c, S, prec, c->V + (size_t)j * len)) != RBM_OK) return s2;
     c->pinned[16 + (j & 1)] = -1.0;
-    HIPCHECK(launch_arnoldi(j, len, c->V, len, c->partial, (size_t)(m + 2) * c->nblk, c->nblk, ldh, c->H,
+    HIPCHECK(launch_arnoldi(j, len, c->V, len, c->part, c->far_nslots, c->partial, (size_t)(m + 2) * c->nblk, c->nblk, ldh, c->H,
                             c->cs, c->sn, c->g, c->pinned_dev + 16 + (j & 1), c->st));
     return RBM_OK;
   };
@@ -1586,7 +1584,7 @@ static rbm_status magnetic_gmres(rbm_ctx* c, double eta, const double* b, double
       if ((s = magnetic_apply(c, eta, c->V + (size_t)k * len, c->V + (size_t)(k + 1) * len)) != RBM_OK)
         return s;
       c->pinned[16] = -1.0;
-      HIPCHECK(launch_arnoldi(k, len, c->V, len, c->partial, (size_t)(m + 2) * c->nblk, c->nblk, ldh, c->H,
+      HIPCHECK(launch_arnoldi(k, len, c->V, len, nullptr, 0, c->partial, (size_t)(m + 2) * c->nblk, c->nblk, ldh, c->H,
                               c->cs, c->sn, c->g, c->pinned_dev + 16, c->st));
       double res;
       if ((s = wait_pinned(c, c->pinned + 16, &res)) != RBM_OK) return s;
