@@ -709,8 +709,9 @@ static rbm_status near_correction(rbm_ctx* c, SolveState& S, int kind, const dou
 // bodies of M consecutive points and largest body diameter d_max: leaf level = finest level
 // whose width is >= d_max (at most fmm_max_level), points sorted by leaf.  Leaves the
 // context without a tree (fmm_ready false) when some leaf would hold more than kFmmLeafCap
-// points; the far sums are then direct.
-static rbm_status fmm_build(rbm_ctx* c, int npts, int M, const double* X, const double* Nn, double d_max) {
+// points; the far sums are then direct.  prec: of the sums that follow (the rotation tables serve float32
+// alone: 27 MiB to clear and fill, 40 us).
+static rbm_status fmm_build(rbm_ctx* c, int npts, int M, const double* X, const double* Nn, double d_max, int prec) {
   c->fmm_ready = false;
   hipStream_t st = c->st;
   HIPCHECK(launch_fmm_bounds(npts, X, c->fsrt, c->fbounds, st));
@@ -751,7 +752,7 @@ static rbm_status fmm_build(rbm_ctx* c, int npts, int M, const double* X, const 
   HIPCHECK(hipMemcpyAsync(c->pinned, c->ftoff + ((size_t)1 << (3 * L)), sizeof(int), hipMemcpyDeviceToHost, st));
   HIPCHECK(hipStreamSynchronize(st));
   std::memcpy(&c->fmm_ntask, c->pinned, sizeof(int));
-  if (L >= 2 && c->opt.fmm_order <= kFmmRotOrder)
+  if (prec != 0 && L >= 2 && c->opt.fmm_order <= kFmmRotOrder)
     HIPCHECK(launch_fmm_rotations(c->opt.fmm_order, L, c->opt.fmm_max_level, c->fmm_D, c->frot, st));
   c->fmm_npts = npts;
   c->fmm_ready = true;
@@ -1076,7 +1077,7 @@ static rbm_status solve_impl(rbm_ctx* c, const double* dFT, double* dVW, rbm_sol
   Timer total(c);
   // tree of the fast multipole far field for the inner iterations at these poses
   if (c->opt.fmm_order > 0 && c->opt.precision != RBM_FP64) {
-    if ((s = fmm_build(c, N, M, c->X, c->Nn, fmm_dmax(c))) != RBM_OK) return s;
+    if ((s = fmm_build(c, N, M, c->X, c->Nn, fmm_dmax(c), 1)) != RBM_OK) return s;
   } else {
     c->fmm_ready = false;
   }
@@ -1738,7 +1739,7 @@ extern "C" rbm_status rbm_far_traction_fmm(rbm_ctx* c, int n_points, int M, cons
   if (n_points > c->nmax * c->M) return fail(RBM_E_NOMEM, "more points than the workspace holds");
   if (!(d_max > 0.0) || !std::isfinite(d_max)) return fail(RBM_E_INVAL, "d_max must be > 0");
   rbm_status s;
-  if ((s = fmm_build(c, n_points, M, X, Nrm, d_max)) != RBM_OK) return s;
+  if ((s = fmm_build(c, n_points, M, X, Nrm, d_max, precision)) != RBM_OK) return s;
   if (!c->fmm_ready) return fail(RBM_E_INVAL, "a leaf box would hold more than 4096 points");
   if (level) *level = c->fmm_level;
   if (precision == 0)
