@@ -29,6 +29,7 @@
 
 #include "common.h"
 #include "fmm.h"
+#include "fmm_plan.h"
 #include "kernels.h"
 #include "pair.h"
 
@@ -37,7 +38,6 @@ namespace rbm {
 constexpr int kFmmPMax = kFmmMaxOrder;
 constexpr int kFmmKc = (kFmmPMax + 1) * (kFmmPMax + 2) / 2;          // coefficients, m >= 0
 constexpr int kFmmLeafMax = kFmmLeafCap;                              // points per leaf
-constexpr int kFmmLeafWaves = 16;                                      // waves per leaf work item, at most
 constexpr int kFmmVecs = 343;                                         // displacements in [-3, 3]^3
 
 template <typename T>
@@ -728,9 +728,8 @@ __global__ void __launch_bounds__(1024) k_fmm_leaf(int P, int nb, double lox, do
       const int row = (nk * nb + nj) * nb;
       total += start[row + i1 + 1] - start[row + i0];
     }
-  // this wave's part [from, to) of the concatenated ranges; the expansions cost about as much as
-  // 5 P^2 / 2 sources
-  const int far = far_on ? 5 * P * P / 2 : 0, each = (total + far + nw - 1) / nw;
+  // this wave's part [from, to) of the concatenated ranges
+  const int far = far_on ? fmm_far_cost(P) : 0, each = (total + far + nw - 1) / nw;
   const int from = __builtin_amdgcn_readfirstlane(max(0, wv * each - far));
   const int to = __builtin_amdgcn_readfirstlane(min(total, max(0, (wv + 1) * each - far)));
   int before = 0;
@@ -904,9 +903,7 @@ hipError_t launch_fmm_apply(int P, int L, const double* lo, double D, int N, con
                                                 Lx + lev_off[lev - 1] * 4 * Kc, Lx + lev_off[lev] * 4 * Kc);
     }
   }
-  // waves per work item: 4 where the items alone give every SIMD some (4096 items are 16 waves a
-  // SIMD), more below
-  const int nw = ntask >= 4096 ? 4 : ntask >= 2048 ? 8 : kFmmLeafWaves;
+  const int nw = fmm_leaf_waves(N, ntask, nb * nb * nb, P, far_on);
   if (ntask > 0)
     k_fmm_leaf<T><<<ntask, 64 * nw, 0, st>>>(P, nb, lo[0], lo[1], lo[2], w, N, task, start, perm, Xs,
                                                    Ns, so, far_on ? Lx + lev_off[L] * 4 * Kc : nullptr,
