@@ -94,12 +94,15 @@ struct SymPhase {
 // The grid holds these pairs alone: with a place for every row of the phase half of them
 // would leave at once, and where the number of rows is a multiple of 32 the rest fall on half
 // of the shader engines, which take workgroups in turn (24,000 points, 32 rows: 0.61 ms
-// instead of 0.41).
+// instead of 0.41).  Where phases are a part of the rows, their first and last blocks pair with fewer
+// rows and leave places empty: an odd number of places moves those over all engines, unless it or three times
+// it is next to a multiple of 32 (48 places, float64, 96,010 points: 8.45 -> 6.36 ms).
 #ifdef __HIPCC__
 __host__ __device__
 #endif
 inline int sym_row(int jr, int x, int nb, int h, int rows) {
   if (h + rows >= nb) {  // the phase's blocks are all nb, cyclic
+    if (x > h) return -1;
     const int r = jr - x;
     return r >= 0 ? (r < rows ? r : -1) : (r + nb < rows ? r + nb : -1);
   }
@@ -115,6 +118,10 @@ inline SymPhase sym_phase(const SymPlan& sp, int rows) {
   const int pl = sp.tb / sp.csl, ps = sp.tb / sp.css;
   p.chunks = p.nl * pl + (p.nj - p.nl) * ps;
   p.width = p.nj == sp.nb ? sp.h + 1 : std::min(rows, sp.h + 1);
+  if (rows < sp.nb) {  // see sym_row
+    const auto slow = [](int w) { return w % 32 == 1 || w % 32 == 11 || w % 32 == 21 || w % 32 == 31; };
+    for (p.width |= 1; slow(p.width); p.width += 2) {}
+  }
   p.slots = (1 + sp.h) * pl + (ps - pl) * std::min(1 + sp.h, p.nj - p.nl);
   return p;
 }
@@ -163,6 +170,14 @@ inline SymPlan sym_plan(int N, int kind, int prec, size_t cap) {
   const int upto[kClasses] = {32000, 50000, 100000, 300000, 2147483647};
   const int c768[kClasses][3] = {{192, 64, 75}, {384, 128, 85}, {768, 128, 80}, {768, 192, 85}, {768, 192, 90}};
   const int c1024[kClasses][3] = {{128, 64, 75}, {256, 128, 80}, {512, 128, 80}, {512, 256, 90}, {1024, 256, 90}};
+  const auto most_rows = [&] {  // that fit
+    int a = 0, b = sp.nb;
+    while (a < b) {
+      const int mid = a + (b - a + 1) / 2;
+      if (sym_need(sp, mid, nv) <= cap) a = mid; else b = mid - 1;
+    }
+    return a;
+  };
   int cls = 0, lo = 0;
   while (N >= upto[cls]) ++cls;
   for (;; ++cls) {
@@ -170,22 +185,36 @@ inline SymPlan sym_plan(int N, int kind, int prec, size_t cap) {
     sp.csl = cls == 4 && sp.tb == 1536 ? 1536 : c[0];
     sp.css = c[1];
     sp.lead = c[2];
-    lo = 0;
-    int hi = sp.nb;  // most rows that fit
-    while (lo < hi) {
-      const int mid = lo + (hi - lo + 1) / 2;
-      if (sym_need(sp, mid, nv) <= cap) lo = mid; else hi = mid - 1;
-    }
+    lo = most_rows();
     if (lo == sp.nb || cls == kClasses - 1 || (cls == 3 && lo > 0)) break;
   }
-  if (lo < 1) return SymPlan{};
-  const int phases = (sp.nb + lo - 1) / lo;
-  sp.rows = (sp.nb + phases - 1) / phases;
-  // every phase drains the chip once: two rounds of 512 long chunks in each, or the ordered
-  // sum; and the grid's second dimension holds 65,535 chunks
-  if ((phases > 1 && (long)sp.rows * (1 + sp.h) * (sp.tb / sp.csl) < 2 * 512) || sym_phase(sp, sp.rows).chunks > 65535)
-    return SymPlan{};
-  return sp;
+  const auto finish = [&] {  // equal phases; false: not worth it
+    if (lo < 1) return false;
+    const int phases = (sp.nb + lo - 1) / lo;
+    sp.rows = (sp.nb + phases - 1) / phases;
+    // every phase drains the chip once: two rounds of 512 long chunks in each, or the ordered
+    // sum; and the grid's second dimension holds 65,535 chunks
+    return (phases == 1 || (long)sp.rows * (1 + sp.h) * (sp.tb / sp.csl) >= 2 * 512) &&
+           sym_phase(sp, sp.rows).chunks <= 65535;
+  };
+  // Phases of few rounds of the resident workgroups (5 a CU in float32, 2 in float64), which only the traction
+  // sum of the no-allocation entry point has: half the long chunk and more short ones, or each phase ends
+  // on a nearly empty round.  Ordered pairs per ns without and with it: float64 112,606 points 1.32 -> 1.50, 190,148 1.41
+  // -> 1.54, 400,009 1.42 -> 1.53 (ordered sum 1.25); float32 69,001 2.56 -> 2.77, 93,044 2.58 -> 2.76, 134,224
+  // 2.82 -> 2.83, from 150,000 on no more: 250,007 2.90 -> 2.84 (ordered sum 2.69).
+  if (lo > 0 && lo < sp.nb && kind == 0 && (!prec || N < 150000) &&
+      (long)lo * (1 + sp.h) * (sp.tb / sp.csl) < 8 * 256 * (prec ? 5 : 2)) {
+    const SymPlan coarse = sp;
+    const int rows = lo;
+    sp.csl = sp.tb / 2;
+    sp.css = prec ? 128 : 192;
+    sp.lead = prec ? 80 : 70;
+    lo = most_rows();
+    if (finish()) return sp;
+    sp = coarse;
+    lo = rows;
+  }
+  return finish() ? sp : SymPlan{};
 }
 
 }  // namespace rbm
