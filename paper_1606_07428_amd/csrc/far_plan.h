@@ -78,6 +78,27 @@ inline int far_packing_slots(int N) {
   return std::max({1, (N + 255) / 256, fill});
 }
 
+// ---- the entry point that allocates nothing (rbm_static.cpp) -----------------------------
+// Bytes of scratch per GPU, and those that one slot of the ordered sum may take, which set the largest input.
+constexpr size_t kStaticBytes = (size_t)192 << 20, kStaticOneSlot = (size_t)64 << 20;
+
+constexpr size_t static_align(size_t bytes) { return (bytes + 255) & ~(size_t)255; }
+
+// Scratch of the ordered sum: packed sources, the slots' partial sums, float32 copies of the targets (prec 1).
+inline size_t static_bytes(size_t N, int slots, int prec) {
+  return static_align(N * (prec == 0 ? 64 : 32)) + static_align((size_t)slots * 3 * N * sizeof(double)) +
+         (prec == 0 ? 0 : 2 * static_align(3 * N * sizeof(float)));
+}
+
+// The context's split, lowered until it fits: not below 36,000 points, and above in float32 only for
+// the few sizes whose unordered pairs do not fit.  (Within 64 MiB instead of all: one slot from 600,000 float64 points
+// on, whose sweep of all sources leaves L2: 720,000 points 448 -> 412 ms.)
+inline int static_split(int N, int prec) {
+  int split = far_split(N);
+  while (split > 1 && static_bytes((size_t)N, split, prec) > kStaticBytes) --split;
+  return split;
+}
+
 // ---- sums with every unordered pair of points evaluated once (k_far_sym.hip) -----------
 // nb blocks of tb points; block row i pairs with the h next blocks (cyclic), rows of the nb in
 // phases of `rows`.  In a phase that starts at row0 the blocks row0 .. row0 + nj - 1 (cyclic) are

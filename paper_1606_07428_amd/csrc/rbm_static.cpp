@@ -21,13 +21,10 @@ using namespace rbm;
 
 namespace {
 
-// Per GPU.  The ordered sum keeps to the first 64 MiB, which also set the largest input; the
-// sums that take every pair once use all of it.
-constexpr size_t kScratchBytes = size_t(192) << 20, kOrderedBytes = size_t(64) << 20;
 constexpr int kMaxDevices = 64;
 
 // Every GPU the library runs on holds its own copy until the process ends.
-__device__ __align__(256) unsigned char scratch[kScratchBytes];
+__device__ __align__(256) unsigned char scratch[kStaticBytes];
 
 std::mutex g_mu;
 unsigned char* g_scratch[kMaxDevices] = {};  // device address of `scratch`, per device
@@ -51,16 +48,6 @@ rbm_status scratch_address(unsigned char** out) {
   return RBM_OK;
 }
 
-size_t align256(size_t b) { return (b + 255) & ~size_t(255); }
-
-// Bytes of scratch for N points, `split` source chunks, precision prec.
-size_t scratch_bytes(size_t N, int split, int prec) {
-  const size_t src = align256(N * (prec == 0 ? 64 : 32));
-  const size_t part = align256((size_t)split * 3 * N * sizeof(double));
-  const size_t f32 = prec == 0 ? 0 : 2 * align256(3 * N * sizeof(float));
-  return src + part + f32;
-}
-
 }  // namespace
 
 extern "C" rbm_status rbm_far_traction_static(int n_points, int M, const double* X, const double* Nrm,
@@ -70,7 +57,7 @@ extern "C" rbm_status rbm_far_traction_static(int n_points, int M, const double*
   if (n_points < 1 || M < 1) return set_last_error(RBM_E_INVAL, "sizes must be >= 1");
   if (precision != 0 && precision != 1) return set_last_error(RBM_E_INVAL, "precision must be 0 or 1");
   const size_t N = (size_t)n_points;
-  if (scratch_bytes(N, 1, precision) > kOrderedBytes)
+  if (static_bytes(N, 1, precision) > kStaticOneSlot)
     return set_last_error(RBM_E_NOMEM, "more points than the static scratch takes (about 762,000 in "
                                        "float64, 838,000 in float32)");
   unsigned char* base = nullptr;
@@ -79,10 +66,10 @@ extern "C" rbm_status rbm_far_traction_static(int n_points, int M, const double*
   hipStream_t st = static_cast<hipStream_t>(stream);
   hipError_t e;
   // every unordered pair once, as in the context path, where the plan's scratch fits
-  const size_t b_src = align256(N * (precision == 0 ? 64 : 32)), b_nor = align256(N * (precision == 0 ? 32 : 16)),
-               b_out = align256(3 * N * sizeof(double)), front = b_src + b_nor + b_out;
-  if (front < kScratchBytes) {
-    const SymPlan sp = sym_plan(n_points, 0, precision, std::min(sym_cap(N), (kScratchBytes - front) / sizeof(double)));
+  const size_t b_src = static_align(N * (precision == 0 ? 64 : 32)), b_nor = static_align(N * (precision == 0 ? 32 : 16)),
+               b_out = static_align(3 * N * sizeof(double)), front = b_src + b_nor + b_out;
+  if (front < kStaticBytes) {
+    const SymPlan sp = sym_plan(n_points, 0, precision, std::min(sym_cap(N), (kStaticBytes - front) / sizeof(double)));
     if (sp.rows > 0) {
       void *src = base, *nor = base + b_src;
       double* sum = reinterpret_cast<double*>(base + b_src + b_nor);
@@ -99,11 +86,9 @@ extern "C" rbm_status rbm_far_traction_static(int n_points, int M, const double*
       return e == hipSuccess ? RBM_OK : set_last_error(RBM_E_DEVICE, hipGetErrorString(e));
     }
   }
-  // the split of the context path, lowered until the partial sums fit
-  int split = far_split(n_points);
-  while (split > 1 && scratch_bytes(N, split, precision) > kOrderedBytes) --split;
+  int split = static_split(n_points, precision);
   void* src = base;
-  double* part = reinterpret_cast<double*>(base + align256(N * (precision == 0 ? 64 : 32)));
+  double* part = reinterpret_cast<double*>(base + static_align(N * (precision == 0 ? 64 : 32)));
   if (far_packing_slots(n_points) > 0) {
     split = far_packing_slots(n_points);
     if ((e = launch_far_packing(0, precision, n_points, M, X, Nrm, nullptr, nullptr, q, 0, part, st)) != hipSuccess)
@@ -113,9 +98,9 @@ extern "C" rbm_status rbm_far_traction_static(int n_points, int M, const double*
         (e = launch_far<double>(0, n_points, M, X, Nrm, src, part, split, st)) != hipSuccess)
       return set_last_error(RBM_E_DEVICE, hipGetErrorString(e));
   } else {
-    unsigned char* f = reinterpret_cast<unsigned char*>(part) + align256((size_t)split * 3 * N * sizeof(double));
+    unsigned char* f = reinterpret_cast<unsigned char*>(part) + static_align((size_t)split * 3 * N * sizeof(double));
     float* Xf = reinterpret_cast<float*>(f);
-    float* Nf = reinterpret_cast<float*>(f + align256(3 * N * sizeof(float)));
+    float* Nf = reinterpret_cast<float*>(f + static_align(3 * N * sizeof(float)));
     if ((e = launch_cast_f32(3 * N, X, Xf, st)) != hipSuccess || (e = launch_cast_f32(3 * N, Nrm, Nf, st)) != hipSuccess ||
         (e = launch_pack_sources<float>(n_points, M, X, nullptr, nullptr, q, 0, nullptr, src, nullptr, st)) != hipSuccess ||
         (e = launch_far<float>(0, n_points, M, Xf, Nf, src, part, split, st)) != hipSuccess)
