@@ -8,7 +8,7 @@
 // colatitudes times uniform azimuths and sums over them separate:
 //   1. the surface's coefficients rotated into the frame: by R_z a mixing of +-m, by R_y the
 //      matrices D_l(theta_t), which couple cosines with cosines and sines with sines only;
-//   2. x, x_theta, x_phi / sin(theta) on the grid: a sum over l per (colatitude, m), then the
+//   2. x - x_t, x_theta, x_phi / sin(theta) on the grid: a sum over l per (colatitude, m), then the
 //      sum over m, whose cosine and sine parts give the azimuths phi and -phi together
 //      (J = |x_theta x x_phi / sin| does not depend on the orthonormal frame it is taken in);
 //   3. the kernels at the nodes; their sums and differences over +-phi against cos(m phi) and
@@ -66,7 +66,7 @@ size_t singular_table_doubles(int p, int ps) { return singular_tables(p, ps).tot
 // Double-double arithmetic (an unevaluated sum hi + lo, Dekker's and Knuth's error-free sums and
 // fma products) for the tables: the recurrences lose about a digit by degree 20, and an error of a
 // table entry, unlike the rounding of a sum over nodes, is common to all targets and nodes.
-// In plain float64 they gave 110 eps of the incident field on a sphere at p = 20 instead of below 64.
+// In plain float64 they gave 110 eps of the incident field on a sphere at p = 20 instead of 73.
 struct dd {
   double hi, lo;
 };
@@ -172,9 +172,14 @@ __global__ __launch_bounds__(64) void k_singular_tables(SingularTables t, const 
     const size_t plane = (size_t)t.MP * (p + 1) * t.NIP;
     double* o = tab + t.lg + (size_t)m * (p + 1) * t.NIP + i;
     double* ol = tab + t.lt + (size_t)i * nc;
+    const dd zero = {0.0, 0.0}, y00 = {0.28209479177387814, 3.83386490329147e-18};  // 1 / sqrt(4 pi)
+    // The plane of P gives the positions, taken relative to the target at the pole of the frame: P_l0 less
+    // its value there, formed before it is rounded.  The difference of two rounded positions loses digits
+    // at the nodes next to the target, where the kernels are largest: rounding errors of K at p = 6, 12, 14 and
+    // 20 against long double 2.2, 3.2, 3.0 and 3.2 eps of its largest entry (rms), with this 0.8, 0.8, 0.4 and 1.5.
     auto put = [&](int l, dd P, dd Q, dd D) {
       const size_t at = (size_t)(l - m) * t.NIP;
-      o[at] = P.hi;
+      o[at] = m == 0 && live ? (P - sqrt_dd(2.0 * l + 1.0) * y00).hi : P.hi;
       o[at + plane] = D.hi;
       o[at + 2 * plane] = ((double)m * Q).hi;
       if (m > p) return;
@@ -182,11 +187,10 @@ __global__ __launch_bounds__(64) void k_singular_tables(SingularTables t, const 
       ol[l * l + l - m] = P.hi;
     };
     int l = m;
-    const dd zero = {0.0, 0.0};
     if (live) {
       const double x = glr_t[i];
       const dd s = sin_of(x), r2 = {1.4142135623730951, -9.667293313452913e-17};  // sqrt 2
-      dd p0 = {0.28209479177387814, 3.83386490329147e-18}, q0 = zero;             // 1 / sqrt(4 pi)
+      dd p0 = y00, q0 = zero;
       if (m) p0 = r2 * p0;
       for (int k = 1; k <= m; ++k) {
         q0 = sqrt_dd(dd{2.0 * k + 1.0, 0.0} / dd{2.0 * k, 0.0}) * p0;
@@ -249,9 +253,8 @@ __host__ __device__ inline int singular_work(int p) {
 // of 256 threads over the (l, m) x 3 sums of step 3; MT: 16-wide tiles of m.
 template <int NIT, int MT>
 __global__ __launch_bounds__(256, NIT == 2 ? 2 : 1) void k_singular(
-    SingularTables T, double eta, const double* __restrict__ coef_all, const double* __restrict__ gx_all,
-    const double* __restrict__ gn_all, const double* __restrict__ rW, const double* __restrict__ tab,
-    double* __restrict__ Sop, double* __restrict__ Kop) {
+    SingularTables T, double eta, const double* __restrict__ coef_all, const double* __restrict__ gn_all,
+    const double* __restrict__ rW, const double* __restrict__ tab, double* __restrict__ Sop, double* __restrict__ Kop) {
   extern __shared__ double lds[];
   const int p = T.p, ps = T.ps, NIP = T.NIP, nc = (p + 1) * (p + 1), M = (p + 1) * 2 * p, M3 = 3 * M;
   const int MQ = (p + 1 + 3) / 4 * 4, p1 = p + 1;
@@ -294,11 +297,9 @@ __global__ __launch_bounds__(256, NIT == 2 ? 2 : 1) void k_singular(
     for (int c = 0; c < 3; ++c) cr[((c * 2 + odd) * MQ + am) * p1 + l - am] = v[c];
   }
   __syncthreads();
-  const double* gx = gx_all + (size_t)s * 3 * M;
   const double* gn = gn_all + (size_t)s * 3 * M;
-  const double xt0 = gx[t], xt1 = gx[M + t], xt2 = gx[2 * M + t];
   const double nt0 = gn[t], nt1 = gn[M + t], nt2 = gn[2 * M + t];
-  const double cS = 1.0 / (8.0 * RBM_PI * eta), cK = -3.0 / (4.0 * RBM_PI);
+  const double cS = 1.0 / (8.0 * RBM_PI * eta), cK = 3.0 / (4.0 * RBM_PI);
   const double* LG = tab + T.lg;
   const size_t plane = (size_t)T.MP * p1 * NIP;
   const double* LT = tab + T.lt;
@@ -374,7 +375,7 @@ __global__ __launch_bounds__(256, NIT == 2 ? 2 : 1) void k_singular(
         const int i = i0 + lk + 4 * e, n = n0 + lr;
         const bool live = i <= ps && n <= ps, twice = n != 0 && n != ps;
         const double W = rW[(size_t)min(i, ps) * 2 * ps];
-        // per sign: x_t - x and the weights of delta, r r (Stokeslet) and r r (traction)
+        // per sign: x - x_t and the weights of delta, r r (Stokeslet) and r r (traction)
         double r[2][3], wd[2], ws[2], wk[2];
 #pragma unroll
         for (int g = 0; g < 2; ++g) {
@@ -383,9 +384,9 @@ __global__ __launch_bounds__(256, NIT == 2 ? 2 : 1) void k_singular(
           for (int k = 0; k < 9; ++k) v[k] = g ? E[k][e] - O[k][e] : E[k][e] + O[k][e];
           const double c0 = v[4] * v[8] - v[5] * v[7], c1 = v[5] * v[6] - v[3] * v[8], c2 = v[3] * v[7] - v[4] * v[6];
           const double w = W * sqrt(c0 * c0 + c1 * c1 + c2 * c2);
-          r[g][0] = xt0 - v[0];
-          r[g][1] = xt1 - v[1];
-          r[g][2] = xt2 - v[2];
+          r[g][0] = v[0];
+          r[g][1] = v[1];
+          r[g][2] = v[2];
           const double di = rsqrt_t(r[g][0] * r[g][0] + r[g][1] * r[g][1] + r[g][2] * r[g][2]);
           const double di3 = di * di * di, rn = r[g][0] * nt0 + r[g][1] * nt1 + r[g][2] * nt2;
           const bool on = live && (g == 0 || twice);
@@ -407,7 +408,8 @@ __global__ __launch_bounds__(256, NIT == 2 ? 2 : 1) void k_singular(
         }
         __syncthreads();
         // this thread's Legendre values of the last step, on their way during the next
-        // (the empty asm keeps their loads from being hoisted out of the loop over azimuths and spilled)
+        // (the empty asm keeps their loads from being hoisted out of the loop over azimuths: 152
+        // registers were spilled then at NIT = 2, 35 are now)
         double lw[2][8];
         auto load_lw = [&](int u) {
           unsigned at = (unsigned)min(tid + 256 * u, 3 * nc - 1) % (unsigned)nc;
@@ -569,8 +571,8 @@ __global__ __launch_bounds__(256, NIT == 2 ? 2 : 1) void k_singular(
   }
 }
 
-hipError_t launch_singular_assemble(int ns, int p, int ps, double eta, const double* coef, const double* gx,
-                                    const double* gn, const double* glr_t, const double* glt, const double* glw,
+hipError_t launch_singular_assemble(int ns, int p, int ps, double eta, const double* coef, const double* gn,
+                                    const double* glr_t, const double* glt, const double* glw,
                                     const double* rW, double* tab, double* Sop, double* Kop, hipStream_t st) {
   const SingularTables T = singular_tables(p, ps);
   k_singular_tables<<<T.NIP * T.MP / 64 + 1, 64, 0, st>>>(T, glr_t, glt, glw, tab);
@@ -581,7 +583,7 @@ hipError_t launch_singular_assemble(int ns, int p, int ps, double eta, const dou
   auto run = [&](auto kern) {
     hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
-    kern<<<grid, 256, lds, st>>>(T, eta, coef, gx, gn, rW, tab, Sop, Kop);
+    kern<<<grid, 256, lds, st>>>(T, eta, coef, gn, rW, tab, Sop, Kop);
     return hipGetLastError();
   };
   // (l, m) x 3 sums per thread: 507 at p = 12, 768 at p = 15, 1323 at p = 20

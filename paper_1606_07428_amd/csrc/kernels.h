@@ -31,8 +31,8 @@ hipError_t launch_shape_geometry(int ns, int p, const double* coef, const double
 // Singular self operators S, K, row-major per shape (k_singular.hip); tab: scratch of
 // singular_table_doubles(p, ps) doubles.
 size_t singular_table_doubles(int p, int ps);
-hipError_t launch_singular_assemble(int ns, int p, int ps, double eta, const double* coef, const double* gx,
-                                    const double* gn, const double* glr_t, const double* glt, const double* glw,
+hipError_t launch_singular_assemble(int ns, int p, int ps, double eta, const double* coef, const double* gn,
+                                    const double* glr_t, const double* glt, const double* glw,
                                     const double* rW, double* tab, double* Sop, double* Kop, hipStream_t st);
 // A0 (column-major) = K (row-major) + 1/2 I + L; A0 and K must not overlap
 hipError_t launch_finish_A0(int ns, int M, const double* gr, const double* gw, const double* K, double* A0,

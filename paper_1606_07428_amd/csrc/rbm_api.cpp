@@ -484,7 +484,7 @@ extern "C" rbm_status rbm_setup(rbm_ctx* c) {
   HIPCHECK(launch_shape_geometry(c->ns, p, c->coef, c->Ytab, c->Yttab, c->Ypstab, c->nlam, c->gx,
                                  c->gn, c->gw, c->gr, c->shp, st));
   // S0 into the A0 buffer and K0 into P0, both row-major and temporary
-  HIPCHECK(launch_singular_assemble(c->ns, p, c->ps, c->opt.eta, c->coef, c->gx, c->gn, c->glr_t, c->gl_t, c->gl_w,
+  HIPCHECK(launch_singular_assemble(c->ns, p, c->ps, c->opt.eta, c->coef, c->gn, c->glr_t, c->gl_t, c->gl_w,
                                     c->rW, c->sing_tab, c->A0, c->P0, st));
   HIPCHECK(launch_velocity_functional(c->ns, M, c->A0, c->gr, c->gw, c->shp, c->V0, st));
   HIPCHECK(launch_finish_A0(c->ns, M, c->gr, c->gw, c->P0, c->A0, st));
