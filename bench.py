@@ -59,6 +59,12 @@ FAR_KERNELS = [
     ("k_far<float, traction>", "ms_traction32", "n_traction32", TRACTION_FLOPS_PER_PAIR, FP32_PEAK_TFLOPS,
      ("k_far.hip", "k_far_sym.hip", "pair.h", "far_plan.h")),
 ]
+# the kernels that evaluate them, by number of points (the names above are those of the ordered sums)
+EVALUATED_BY = {
+    "k_far_ts (float64 traction + Stokeslet)": "k_far_sym from 56,000 points, k_far_ts below",
+    "k_far<double, traction>": "k_far_sym from 15,000 points, k_far below (k_far_packing to 10,240 without upsampling)",
+    "k_far<float, traction>": "k_far_sym from 36,000 points, k_far below (k_far_packing to 10,240 without upsampling)",
+}
 
 # Per workload: near-singular upsampling order (0 = plain smooth rule), fast multipole order
 # of the inner far sums (0 = direct float32 sums) and RK4 steps of the training trajectory.
@@ -166,10 +172,12 @@ def _rooflines(infl, ppl, workload):
         avg_s = ms / n / 1e3
         achieved = fpp * ppl / avg_s / 1e12
         traffic = _traffic(name, workload, files)
-        out.append({"bound": "alu", "kernel": name, "achieved": achieved, "peak": peak, "unit": "TFLOP/s",
-                    "frac": achieved / peak, "traffic": traffic["bytes_per_launch"] if traffic else None,
+        out.append({"bound": "alu", "kernel": name, "evaluated_by": EVALUATED_BY[name],
+                    "achieved": achieved, "peak": peak, "unit": "TFLOP/s", "frac": achieved / peak,
+                    "traffic": traffic["bytes_per_launch"] if traffic else None,
                     "traffic_detail": traffic, "launch_ms": avg_s * 1e3, "launches": n,
-                    "pairs_per_launch": ppl, "flops_per_pair": fpp, "total_ms": ms})
+                    "pairs_per_launch": ppl, "flops_per_pair": fpp, "pairs": "ordered (both directions)",
+                    "total_ms": ms})
     out.sort(key=lambda r: -r["total_ms"])
     return out
 

@@ -25,9 +25,10 @@ struct FarChunks {
 // the mean over floor(split / 2) slots, so split >= 1.7 N / kChunkSources + 2 (at 1.25 M
 // points 67 chunks instead of 3).  At most 96, and no fewer than kMinSources sources per
 // chunk: below 24,000 points the sum is a serial sweep of too few workgroups unless the
-// sources are cut finely.  Bounding the split by nbx as well left two workgroups sweeping
+// sources are cut finely.  Bounding the split by nbx as well left k_far two workgroups sweeping
 // 144 sources each at 288 points (51 us; 4.2 us with 36 chunks) and 400 workgroups at 5,003
-// points (89 us; 33 us with 96 chunks).
+// points (89 us; 33 us with 96 chunks); sums of so few points come to it from solves with upsampling
+// and from the Laplace kernels, the others take far_packing_slots below.
 constexpr int kChunkSources = 32768;
 constexpr int kMinSources = 8;
 constexpr int kResident = 2048;  // 4-wave workgroups that 256 CUs hold at once
@@ -90,9 +91,9 @@ inline size_t static_bytes(size_t N, int slots, int prec) {
          (prec == 0 ? 0 : 2 * static_align(3 * N * sizeof(float)));
 }
 
-// The context's split, lowered until it fits: not below 36,000 points, and above in float32 only for
-// the few sizes whose unordered pairs do not fit.  (Within 64 MiB instead of all: one slot from 600,000 float64 points
-// on, whose sweep of all sources leaves L2: 720,000 points 448 -> 412 ms.)
+// The context's split, lowered until it fits.  Below 36,000 points it does; the ordered sum of more is that of
+// the sizes whose unordered pairs do not fit, float64 from about 708,500.  (Within 64 MiB instead of all they had one
+// slot, a sweep of all sources that leaves L2: 720,000 points 448 -> 412 ms.)
 inline int static_split(int N, int prec) {
   int split = far_split(N);
   while (split > 1 && static_bytes((size_t)N, split, prec) > kStaticBytes) --split;
@@ -175,7 +176,7 @@ inline size_t sym_cap(size_t N) {
 // 20,000, 4.04 / 3.75 at 60,000 and 29.0 / 25.5 at 160,000 (its six sums a side leave two waves
 // per SIMD); float32 traction 0.177 / 0.178 at 20,000, 0.606 / 0.572 at 40,000 and 9.34 / 8.41 at
 // 160,000 (its ordered kernel issues nearly two VALU operations per four cycles with eight
-// waves per SIMD, more than the six waves here reach, which eats half of the gain).
+// waves per SIMD, more than the five waves here reach, which eats half of the gain).
 inline SymPlan sym_plan(int N, int kind, int prec, size_t cap) {
   SymPlan sp{};
   const int from = prec ? 36000 : kind == 4 ? 56000 : kSymMin;

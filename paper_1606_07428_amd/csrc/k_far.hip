@@ -234,8 +234,10 @@ template hipError_t launch_pack_sources<float>(int, int, const double*, const do
 // The ordered sum of few points without the launches before it: a workgroup takes 64 targets, packs
 // its chunk of sources into LDS (a thread each) and gives each wave a quarter of them; the waves'
 // sums are added through LDS.  Same operations as the casts, k_pack and k_far.
-// Bound by latency: a launch, the loads, a wave's serial sum; a quarter of the partial sums that one
-// chunk per workgroup of 256 targets writes (5003 points: far_traction_static 43 -> 34 us).
+// Bound at the upper end by VALU issue: 5003 points in float64 are 25.0 million ordered pairs at 24 operations
+// of 4 cycles and a reciprocal square root of 16, 43,000 cycles a SIMD or 20 of the call's 33 us; below
+// 3000 points by latency (a launch, the loads, a wave's serial sum).  A quarter of the partial
+// sums that one chunk per workgroup of 256 targets writes (5003 points: far_traction_static 43 -> 34 us).
 template <typename T, int KIND>
 __global__ __launch_bounds__(256) void k_far_packing(int N, int M, int chunk, const double* __restrict__ X,
                                                      const double* __restrict__ Nn, const double* __restrict__ W,

@@ -440,7 +440,7 @@ static hipError_t sym_run(const SymPlan& sp, int N, int M, const void* src, cons
 // Points per lane (TPL) and the shape of the LDS reduction: TPL as large as the registers of
 // two waves per SIMD allow for the sums that are long enough (the exchange of a source's
 // sums is shared by TPL pairs), three at the sizes where the blocks would be too few;
-// float32 keeps six waves per SIMD with three.
+// float32 traction keeps five waves per SIMD with three (88 registers).
 template <typename T>
 hipError_t launch_far_sym(int kind, const SymPlan& sp, int N, int M, const void* src, const void* nor, double* part,
                           double* out0, double* out1, hipStream_t st) {

@@ -113,12 +113,12 @@ struct SymPlan;
 template <typename T>
 hipError_t launch_far_sym(int kind, const SymPlan& sp, int N, int M, const void* src, const void* nor, double* part,
                           double* out0, double* out1, hipStream_t st);
-// out[3][N] = ca * a[3][N] (optional) + cb * R_i b_body (optional) + cp * sum_s part[s];
-// out may be the same array as a, never as b_body
 // Packing and ordered sum (kind 0, 1) of float64 arrays in one launch into far_packing_slots(N)
 // (far_plan.h) slots, where that is not 0; prec 1: in float32.
 hipError_t launch_far_packing(int kind, int prec, int N, int M, const double* X, const double* Nn, const double* W,
                               const double* Rm, const double* z, int z_is_body, double* part, hipStream_t st);
+// out[3][N] = ca * a[3][N] (optional) + cb * R_i b_body (optional) + cp * sum_s part[s];
+// out may be the same array as a, never as b_body
 hipError_t launch_combine(int N, int M, int nsplit, const double* part, double cp,
                           const double* a, double ca, const double* b_body, const double* Rm,
                           double cb, double* out, hipStream_t st);
