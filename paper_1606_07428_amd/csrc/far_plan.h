@@ -107,6 +107,7 @@ inline int static_split(int N, int prec) {
 // the grid drain, of css.  `slots` bounds the chunks of one row.
 struct SymPlan {
   int tb, nb, h, csl, css, lead, rows;  // lead: per cent of a phase's blocks that take csl
+  bool few;                             // phases of few rounds of the resident workgroups
 };
 struct SymPhase {
   int rows, nj, nl, chunks, slots, width;  // width: most rows of the phase that pair with one block
@@ -118,7 +119,9 @@ struct SymPhase {
 // of the shader engines, which take workgroups in turn (24,000 points, 32 rows: 0.61 ms
 // instead of 0.41).  Where phases are a part of the rows, their first and last blocks pair with fewer
 // rows and leave places empty: an odd number of places moves those over all engines, unless it or three times
-// it is next to a multiple of 32 (48 places, float64, 96,010 points: 8.45 -> 6.36 ms).
+// it is next to a multiple of 32 (48 places, float64, 96,010 points: 8.45 -> 6.36 ms).  In phases of many
+// rounds those blocks weigh little, and the numbers as they are keep more of a row's points in the dies' L2 (fused
+// sum of 415,584 points 171 ms, with odd numbers 174).
 #ifdef __HIPCC__
 __host__ __device__
 #endif
@@ -140,7 +143,7 @@ inline SymPhase sym_phase(const SymPlan& sp, int rows) {
   const int pl = sp.tb / sp.csl, ps = sp.tb / sp.css;
   p.chunks = p.nl * pl + (p.nj - p.nl) * ps;
   p.width = p.nj == sp.nb ? sp.h + 1 : std::min(rows, sp.h + 1);
-  if (rows < sp.nb) {  // see sym_row
+  if (sp.few) {  // see sym_row
     const auto slow = [](int w) { return w % 32 == 1 || w % 32 == 11 || w % 32 == 21 || w % 32 == 31; };
     for (p.width |= 1; slow(p.width); p.width += 2) {}
   }
@@ -224,8 +227,9 @@ inline SymPlan sym_plan(int N, int kind, int prec, size_t cap) {
   // on a nearly empty round.  Ordered pairs per ns without and with it: float64 112,606 points 1.32 -> 1.50, 190,148 1.41
   // -> 1.54, 400,009 1.42 -> 1.53 (ordered sum 1.25); float32 69,001 2.56 -> 2.77, 93,044 2.58 -> 2.76, 134,224
   // 2.82 -> 2.83, from 150,000 on no more: 250,007 2.90 -> 2.84 (ordered sum 2.69).
-  if (lo > 0 && lo < sp.nb && kind == 0 && (!prec || N < 150000) &&
-      (long)lo * (1 + sp.h) * (sp.tb / sp.csl) < 8 * 256 * (prec ? 5 : 2)) {
+  sp.few = lo > 0 && lo < sp.nb && kind == 0 &&
+           (long)lo * (1 + sp.h) * (sp.tb / sp.csl) < 8 * 256 * (prec ? 5 : 2);
+  if (sp.few && (!prec || N < 150000)) {
     const SymPlan coarse = sp;
     const int rows = lo;
     sp.csl = sp.tb / 2;

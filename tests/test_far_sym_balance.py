@@ -55,3 +55,38 @@ def test_phases_are_balanced(tmp_path):
     subprocess.run([gxx, "-O2", "-std=c++17", "-I", CSRC, str(src), "-o", str(exe)], check=True)
     worst, plans = subprocess.run([str(exe)], check=True, capture_output=True, text=True).stdout.split()
     assert float(worst) < 1.1 and int(plans) > 100
+
+
+CONTEXT = r"""
+#include <cstdio>
+#include "far_plan.h"
+using namespace rbm;
+int main() {
+  long bad = 0, plans = 0;
+  for (int kind = 0; kind < 5; ++kind)
+    for (int prec = 0; prec < 2; ++prec)
+      for (int N = 14000; N < 6000000; N += N / 400) {
+        const SymPlan sp = sym_plan(N, kind, prec, sym_cap(N));
+        if (sp.rows < 1) continue;
+        ++plans;
+        const SymPhase ph = sym_phase(sp, sp.rows);
+        if (ph.width != (ph.nj == sp.nb ? sp.h + 1 : std::min(sp.rows, sp.h + 1))) ++bad;
+      }
+  std::printf("%ld %ld\n", bad, plans);
+  return 0;
+}
+"""
+
+
+def test_phases_of_a_context_have_no_spare_places(tmp_path):
+    """A context's scratch gives phases of many rounds: no more places than rows that pair with a block
+    (spare ones move a row's points between the dies' L2 and slowed the fused sum by 1 %)."""
+    gxx = shutil.which("g++")
+    if gxx is None:
+        pytest.skip("g++ not available")
+    src = tmp_path / "context.cpp"
+    src.write_text(CONTEXT)
+    exe = tmp_path / "context"
+    subprocess.run([gxx, "-O2", "-std=c++17", "-I", CSRC, str(src), "-o", str(exe)], check=True)
+    bad, plans = map(int, subprocess.run([str(exe)], check=True, capture_output=True, text=True).stdout.split())
+    assert bad == 0 and plans > 10000
