@@ -835,7 +835,7 @@ static int fmm_threads(int P) {
 }
 
 // Translations by rotation or dense.  At order 12 and 4096 leaves the dense kernel takes 5.1 ms, the
-// rotations 1.52; they have float32 tables, and two tiles of 8 orders each.
+// rotations 1.45; they have float32 tables, and two tiles of 8 orders each.
 template <typename T>
 static constexpr bool fmm_rotates(int P) { return sizeof(T) == 4 && P <= kFmmRotOrder; }
 

@@ -158,7 +158,8 @@ __device__ __forceinline__ float quad(float v) {
 
 // Bound: the 57 KB of tables that a wave reads per displacement (10 GB in all at p = 12 and 4096 leaves,
 // 7.8 TB/s from L2) and the latency of two waves per SIMD; matrix cores 34% busy, vector units about
-// as much.  Operands are loaded two degrees ahead.  5.1 (dense, on the vector units) -> 1.52 ms.  The
+// as much.  Operands are loaded two degrees ahead (256 registers at order 12, 6 spilled).  5.1 (dense, on the
+// vector units) -> 1.45 ms.  The
 // whole sum's rounding error against float64 on the same tree falls from 2.4e-6 to 2.0e-6 (rms).
 // Workgroup: 4 boxes of one octant of a level; its NW waves take every NWth displacement and add their
 // locals through LDS.  (Eight waves: two per SIMD, and enough workgroups to even out over the CUs.)
