@@ -625,7 +625,8 @@ __global__ void __launch_bounds__(1024) k_fmm_leaf(int P, int nb, double lox, do
                                                   const double4* __restrict__ Xs, const double4* __restrict__ Ns,
                                                   const Src8<T>* __restrict__ srt, const Cx<T>* __restrict__ Lleaf,
                                                   int far_on, double* __restrict__ out) {
-  __shared__ T sum[kFmmLeafWaves - 1][3][64];
+  extern __shared__ __align__(8) unsigned char leaf_lds[];
+  T(*sum)[3][64] = reinterpret_cast<T(*)[3][64]>(leaf_lds);  // of the waves after the first
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), nw = blockDim.x >> 6;
   const int lane = threadIdx.x & 63;
   const int2 tk = task[blockIdx.x];
@@ -905,7 +906,7 @@ hipError_t launch_fmm_apply(int P, int L, const double* lo, double D, int N, con
   }
   const int nw = fmm_leaf_waves(N, ntask, nb * nb * nb, P, far_on);
   if (ntask > 0)
-    k_fmm_leaf<T><<<ntask, 64 * nw, 0, st>>>(P, nb, lo[0], lo[1], lo[2], w, N, task, start, perm, Xs,
+    k_fmm_leaf<T><<<ntask, 64 * nw, (nw - 1) * 3 * 64 * sizeof(T), st>>>(P, nb, lo[0], lo[1], lo[2], w, N, task, start, perm, Xs,
                                                    Ns, so, far_on ? Lx + lev_off[L] * 4 * Kc : nullptr,
                                                    far_on ? 1 : 0, out);
   return hipGetLastError();

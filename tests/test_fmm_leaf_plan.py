@@ -1,7 +1,7 @@
-"""Host rule of the fast multipole leaf sums (`csrc/fmm_plan.h`): a power of two of waves, at
-least two, and beyond two never more than the expansions (done by the first wave alone) and the
-sources share out to: a tree of a few points per leaf does not fill the chip with waves that wait.
-Built with g++ from the header alone."""
+"""Host rule of the fast multipole leaf sums (`csrc/fmm_plan.h`): a power of two of waves by the number of
+work items, or down to a quarter of that where the expansions (done by the first wave alone) and the
+sources do not share out to more: a tree of a few points per leaf does not fill the chip with waves
+that wait.  Built with g++ from the header alone."""
 import os
 import shutil
 import subprocess
@@ -27,11 +27,12 @@ int main() {
           const int w = fmm_leaf_waves((int)N, (int)tasks, boxes, P, far_on);
           const double leaves = std::min<double>(boxes, tasks), share = 1 + 27 * N / leaves / (far_on ? fmm_far_cost(P) : 1);
           ++n;
-          if (w < 2 || w > kFmmLeafWaves || (w & (w - 1)) || (w > 2 && w > share)) ++bad;
-          if (tasks >= 4096 && w > 4) ++bad;
+          const int most = tasks >= 4096 ? 4 : tasks >= 2048 ? 8 : kFmmLeafWaves;
+          if (w < most / 4 || w > most || (w & (w - 1)) || (w > most / 4 && w > share)) ++bad;
+          if (w < most && 2 * w <= share) ++bad;
         }
       }
-  if (fmm_leaf_waves(100000, 31919, 32768, 12, true) != 2 || fmm_leaf_waves(71465, 1289, 512, 12, true) != 8 ||
+  if (fmm_leaf_waves(100000, 31919, 32768, 12, true) != 1 || fmm_leaf_waves(71465, 1289, 512, 12, true) != 8 ||
       fmm_leaf_waves(30000, 498, 64, 4, true) != 16 || fmm_leaf_waves(1248000, 21000, 4096, 12, true) != 4 ||
       fmm_leaf_waves(1, 1, 1, 2, false) != 16 || fmm_leaf_waves(5, 0, 1, 2, false) != 16) ++bad;
   std::printf("%ld %ld\n", bad, n);
